@@ -184,14 +184,32 @@ sv_status launch_pack(int dtype, const float *w, int Cout, int Cin, int k, int n
 // (FP32 [n_pad], 0 past Cout)
 sv_status launch_pack_i8(const float *w, int Cout, int Cin, int k, int n_pad, int cin_pad, int8_t *dst,
                          float *scale, hipStream_t s);
-// Weight-gradient partial sums of one layer (the backward's k_wgrad, kernel
-// sizes 1, 3, 5): part[split][o_pad][taps][cinp] then the bias partials
-// part_b[split][o_pad]; dy is the output gradient (FP32 NHWC, pitch dy_pitch).
-struct WgradShape { int splits, o_pad, taps, cinp; };
-size_t wgrad_partial_floats(int B, int Ho, int Wo, int Cin, int Cout, int ks);
-sv_status launch_wgrad_partials(int dtype, int ks, int stride, ConvSrc s0, ConvSrc s1, int B, int Hi, int Wi,
-                                int Ho, int Wo, int Cout, const float *dy, int dy_pitch, float *part,
-                                WgradShape &shape, hipStream_t st);
+// Weight and bias gradient of one layer: dW[o][tap][c] = sum over the output
+// pixels of dy[m][o] x[m shifted by tap][c], kernel sizes 1, 3, 5.  s0 / s1: the
+// input as one or two sources (TENSOR, RESIZE or X0; whole channel groups of
+// 8 each, except a last one of x0).  dy: NHWC in dy_sdt (SV_F32 / SV_BF16 /
+// SV_F16), dy_pitch values a pixel, 16-byte (16-bit types: 8-byte) aligned,
+// the channels to the next multiple of four present.
+// A stride-2 deconvolution's weight gradient is the same sum with the roles
+// exchanged: s0 = its output gradient, "dy" = its input, stride 2, rows = its
+// input channels (GM_SWAP); its bias sums are then those of s0 (bias_src).
+struct WgradJob {
+    int dtype, ks, stride;
+    ConvSrc s0, s1;
+    int B, Hi, Wi, Ho, Wo, Cout;
+    const void *dy;
+    int dy_sdt, dy_pitch;
+    int bias_src;
+};
+// Where the sums go.  GM_OIHW: [row][column][tap] (flip: the tap reversed);
+// GM_SWAP: [column][row][tap]; GM_TAPROWS: rows are the kk taps of a layer with
+// one output; GM_Y: the same for the columns of Table I's upsampling layer;
+// GM_X0: x0's (tap, channel) columns; GM_FE: those of FE_1 and FE_2, whose
+// FE_2 weights lie off1 and biases off2 after FE_1's.
+enum GradMapKind { GM_OIHW = 0, GM_SWAP, GM_TAPROWS, GM_Y, GM_X0, GM_FE };
+struct GradMap { int kind, cin, kk, flip, nbias, off1, off2; };
+size_t wgrad_part_floats(const WgradJob &j);
+sv_status launch_wgrad(const WgradJob &j, const GradMap &m, float *part, float *gw, float *gb, hipStream_t st);
 
 // INT8 pass prologue: zero nslots * AMAX_SUB words, then record the amax of
 // x0 = [scale0 * d, img / 256] over n coarse pixels in slot x0_slot

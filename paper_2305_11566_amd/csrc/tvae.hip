@@ -20,7 +20,6 @@
 #include <algorithm>
 #include <array>
 #include <atomic>
-#include <initializer_list>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -702,6 +701,29 @@ sv_status tv_forward(const TvShape &s, int f, const void *packed, const uint8_t 
 constexpr int DMLC = 8;
 struct TvBwd { size_t dL1, dL2, dL3, dZ, dML, dT, part, sum, total; };
 
+// The weight gradient of launched layer li: its shape and dtype (the caller
+// fills in the sources and the gradient).  The two stride-2 deconvolutions
+// exchange the roles of input and output gradient (see WgradJob): a quarter of
+// the products of the zero-inserted form, whose other three quarters are zeros.
+WgradJob tv_wgrad_job(int dtype, const TvLevels &lv, int B, int li) {
+    static constexpr int kInLevel[T_NL] = {1, 1, 2, 2, 3, 3, 3, 3, 3, 2, 2, 1};
+    const bool deconv = li == T_D2 || li == T_D;
+    const int ki = deconv ? kOutLevel[li] : kInLevel[li], ko = deconv ? kInLevel[li] : kOutLevel[li];
+    WgradJob j{};
+    j.dtype = li == T_YP ? SV_F32 : dtype;
+    j.ks = kLayers[li].k;
+    j.stride = deconv ? 2 : kLayers[li].stride;
+    j.B = B;
+    j.Hi = lv.h[ki]; j.Wi = lv.w[ki];
+    j.Ho = lv.h[ko]; j.Wo = lv.w[ko];
+    j.Cout = deconv ? kLayers[li].cin : kLayers[li].cout;
+    j.s0.C = deconv ? kLayers[li].cout : kLayers[li].cin;
+    j.s0.kind = li == T_FE ? SRC_X0 : SRC_TENSOR;
+    j.dy_sdt = SV_F32;
+    j.bias_src = deconv;
+    return j;
+}
+
 TvBwd tv_bwd_layout(const TvShape &s, const TvLevels &lv, int B) {
     auto px = [&](int k) { return (size_t)B * lv.h[k] * lv.w[k]; };
     TvBwd l{};
@@ -715,14 +737,10 @@ TvBwd tv_bwd_layout(const TvShape &s, const TvLevels &lv, int B) {
     l.dT = take(px(1) * TC);
     // weight-gradient partial sums of the largest layer (layers run one after another)
     size_t mx = 0;
-    for (int i = 0; i < T_NL; ++i) {
-        const int k = kOutLevel[i];
-        mx = std::max(mx, wgrad_partial_floats(B, lv.h[k], lv.w[k], kLayers[i].cin, kLayers[i].cout, kLayers[i].k));
-    }
+    for (int i = 0; i < T_NL; ++i) mx = std::max(mx, wgrad_part_floats(tv_wgrad_job(s.dtype, lv, B, i)));
     l.part = take(mx);
     l.sum = take(256 + 1);
     l.total = o;
-    (void)s;
     return l;
 }
 
@@ -799,39 +817,6 @@ __global__ void k_tv_reparam_bwd(const float *__restrict__ dz, const float *__re
     for (int c = 2; c < DMLC; ++c) o[c] = 0.f;
 }
 
-// Canonical weight and bias gradient of one canonical layer from the partial
-// sums of the launched layer's weight gradient: row = row0 + o (proj: the
-// tap), tap = the canonical tap (flipped for a deconvolution's stride-1 form),
-// column = cmap[canonical input channel].
-struct GradJob {
-    int cout, cin, k, row0, flip, proj, bias;
-    int splits, o_pad, taps, cinp;
-    int cmap[96];
-};
-
-__global__ void k_tv_grad_reduce(const GradJob j, const float *__restrict__ part, float *__restrict__ grad) {
-    const int kk = j.k * j.k;
-    const int nw = j.cout * j.cin * kk;
-    const int n = nw + (j.bias ? j.cout : 0);
-    const float *part_b = part + (size_t)j.splits * j.o_pad * j.taps * j.cinp;
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gridDim.x * blockDim.x) {
-        float acc = 0.f;
-        if (e < nw) {
-            const int o = e / (j.cin * kk), ci = (e / kk) % j.cin, t = e % kk;
-            const int col = j.cmap[ci];
-            const int row = j.proj ? t : j.row0 + o;
-            const int tap = j.proj ? 0 : (j.flip ? kk - 1 - t : t);
-            if (col >= 0)
-                for (int sp = 0; sp < j.splits; ++sp)
-                    acc += part[(((size_t)sp * j.o_pad + row) * j.taps + tap) * j.cinp + col];
-        } else {
-            const int o = e - nw;
-            for (int sp = 0; sp < j.splits; ++sp) acc += part_b[(size_t)sp * j.o_pad + j.row0 + o];
-        }
-        grad[e] = acc;
-    }
-}
-
 ConvSrc fsrc(const float *p, int C, int pitch, int coff, int hs, int ws, int kind) {
     return tsrc(p, C, pitch, coff, hs, ws, kind, SDT_F32);
 }
@@ -877,31 +862,25 @@ sv_status tv_backward(const TvShape &s, int f, const void *packed, const uint8_t
     x0.scale0 = (float)f / 256.0f;
     auto blocks = [](size_t n) { return (unsigned)std::min<size_t>((n + 255) / 256, 4096); };
 
-    // weight gradient of launched layer li into the canonical slices of `jobs`
-    auto wgrad = [&](int li, int ks, int stride, ConvSrc s0, ConvSrc s1, int Hi, int Wi, int Ho, int Wo,
-                     const float *dy, int dy_pitch, std::initializer_list<GradJob> jobs,
-                     std::initializer_list<int> canons) -> sv_status {
-        WgradShape sh{};
-        SV_TRY_STATUS(launch_wgrad_partials(li == T_YP ? SV_F32 : s.dtype, ks, stride, s0, s1, B, Hi, Wi, Ho, Wo,
-                                            kLayers[li].cout, dy, dy_pitch, part, sh, st));
-        auto cit = canons.begin();
-        for (GradJob j : jobs) {
-            j.splits = sh.splits; j.o_pad = sh.o_pad; j.taps = sh.taps; j.cinp = sh.cinp;
-            const int n = j.cout * j.cin * j.k * j.k + (j.bias ? j.cout : 0);
-            hipLaunchKernelGGL(k_tv_grad_reduce, dim3(cdiv(n, 256)), dim3(256), 0, st, j, part, grad + canon_off(*cit));
-            SV_LAUNCH_CHECK("k_tv_grad_reduce");
-            ++cit;
+    // weight and bias gradient of launched layer li into its canonical slice
+    auto wgrad = [&](int li, int canon, ConvSrc s0, ConvSrc s1, const void *dy, int dy_pitch) -> sv_status {
+        WgradJob j = tv_wgrad_job(s.dtype, lv, B, li);
+        j.s0 = s0; j.s1 = s1;
+        j.dy = dy; j.dy_pitch = dy_pitch;
+        const CanonLayer &c = kCanon[canon];
+        GradMap m{};
+        m.kind = j.bias_src ? GM_SWAP : (li == T_YP ? GM_Y : (li == T_FE ? GM_FE : GM_OIHW));
+        m.cin = c.cin;
+        m.kk = c.k * c.k;
+        m.nbias = li == T_YP ? 0 : c.cout;
+        if (j.bias_src) j.dy_sdt = s.dtype;  // the deconvolution's input, as it is stored
+        if (li == T_FE) {
+            m.nbias = kLayers[T_FE].cout;
+            m.off1 = m.off2 = (int)(canon_off(C_FE2) - canon_off(C_FE1));
         }
-        return SV_OK;
+        float *gw = grad + canon_off(canon);
+        return launch_wgrad(j, m, part, gw, gw + (size_t)c.cout * c.cin * c.k * c.k, st);
     };
-    auto job = [&](int canon, int row0, bool flip, auto colmap) {
-        GradJob j{};
-        j.cout = kCanon[canon].cout; j.cin = kCanon[canon].cin; j.k = kCanon[canon].k;
-        j.row0 = row0; j.flip = flip; j.proj = canon == C_Y; j.bias = canon != C_Y;
-        for (int q = 0; q < 96; ++q) j.cmap[q] = q < j.cin ? colmap(q) : -1;
-        return j;
-    };
-    auto idc = [](int q) { return q; };
     auto mask = [&](float *g, int gpitch, int gcoff, const void *act, int apitch, int acoff, int C, size_t npix) -> sv_status {
         switch (s.dtype) {
         case SV_F32: hipLaunchKernelGGL(k_tv_mask<SV_F32>, dim3(blocks(npix * C)), dim3(256), 0, st, g, gpitch, gcoff, (const float *)act, apitch, acoff, C, npix); break;
@@ -918,76 +897,63 @@ sv_status tv_backward(const TvShape &s, int f, const void *packed, const uint8_t
     hipLaunchKernelGGL(k_tv_sum_partial, dim3(256), dim3(256), 0, st, dout, (int64_t)B * H * W, sum);
     hipLaunchKernelGGL(k_tv_sum_final, dim3(1), dim3(256), 0, st, sum, 256.0f, grad + canon_off(C_Y) + 81 * 25);
     SV_LAUNCH_CHECK("k_tv_sum");
-    SV_TRY_STATUS(wgrad(T_YP, 1, 1, tsrc(L1, 80, L1C, 0, h1, w1, SRC_TENSOR, sdt), x0, h1, w1, h1, w1, dT, TC,
-                        {job(C_Y, 0, false, [](int q) { return q < 16 ? q : (q == 16 ? 80 : q - 1); })}, {C_Y}));
+    SV_TRY_STATUS(wgrad(T_YP, C_Y, tsrc(L1, 80, L1C, 0, h1, w1, SRC_TENSOR, sdt), x0, dT, TC));
     SV_TRY_STATUS(tv_dgrad(s, packed, T_YP, fsrc(dT, TV_TAPS, TC, 0, h1, w1, SRC_TENSOR), 1, B, h1, w1, h1, w1,
                            dL1, L1C, 0, false, st));
     // D (deconvolution into level 1)
     SV_TRY_STATUS(mask(dL1, L1C, 0, L1, L1C, 0, 16, p1));
-    SV_TRY_STATUS(wgrad(T_D, 5, 1, tsrc(L2, 48, L2C, 0, h2, w2, SRC_ZINS, 0), none, 2 * h2 - 1, 2 * w2 - 1, h1, w1,
-                        dL1, L1C, {job(C_D, 0, true, idc)}, {C_D}));
+    SV_TRY_STATUS(wgrad(T_D, C_D, fsrc(dL1, 16, L1C, 0, h1, w1, SRC_TENSOR), none, L2, L2C));
     SV_TRY_STATUS(tv_dgrad(s, packed, T_D, fsrc(dL1, 16, L1C, 0, h1, w1, SRC_TENSOR), 2, B, h1, w1, h2, w2,
                            dL2, L2C, 0, false, st));
     // D_2_R
     SV_TRY_STATUS(mask(dL2, L2C, 40, L2, L2C, 40, 8, p2));
-    SV_TRY_STATUS(wgrad(T_D2R, 5, 1, tsrc(L2, 40, L2C, 0, h2, w2, SRC_TENSOR, 0), none, h2, w2, h2, w2, dL2 + 40, L2C,
-                        {job(C_D2R, 0, false, idc)}, {C_D2R}));
+    SV_TRY_STATUS(wgrad(T_D2R, C_D2R, tsrc(L2, 40, L2C, 0, h2, w2, SRC_TENSOR, 0), none, dL2 + 40, L2C));
     SV_TRY_STATUS(tv_dgrad(s, packed, T_D2R, fsrc(dL2, 8, L2C, 40, h2, w2, SRC_TENSOR), 1, B, h2, w2, h2, w2,
                            dL2, L2C, 0, true, st));
     // D_2 (deconvolution into level 2)
     SV_TRY_STATUS(mask(dL2, L2C, 0, L2, L2C, 0, 16, p2));
-    SV_TRY_STATUS(wgrad(T_D2, 5, 1, tsrc(L3, 96, L3C, 0, h3, w3, SRC_ZINS, 0), none, 2 * h3 - 1, 2 * w3 - 1, h2, w2,
-                        dL2, L2C, {job(C_D2, 0, true, idc)}, {C_D2}));
+    SV_TRY_STATUS(wgrad(T_D2, C_D2, fsrc(dL2, 16, L2C, 0, h2, w2, SRC_TENSOR), none, L3, L3C));
     SV_TRY_STATUS(tv_dgrad(s, packed, T_D2, fsrc(dL2, 16, L2C, 0, h2, w2, SRC_TENSOR), 2, B, h2, w2, h3, w3,
                            dL3, L3C, 0, false, st));
     // D_1_R
     SV_TRY_STATUS(mask(dL3, L3C, 80, L3, L3C, 80, 16, p3));
-    SV_TRY_STATUS(wgrad(T_D1R, 5, 1, tsrc(L3, 80, L3C, 0, h3, w3, SRC_TENSOR, 0), none, h3, w3, h3, w3, dL3 + 80, L3C,
-                        {job(C_D1R, 0, false, idc)}, {C_D1R}));
+    SV_TRY_STATUS(wgrad(T_D1R, C_D1R, tsrc(L3, 80, L3C, 0, h3, w3, SRC_TENSOR, 0), none, dL3 + 80, L3C));
     SV_TRY_STATUS(tv_dgrad(s, packed, T_D1R, fsrc(dL3, 16, L3C, 80, h3, w3, SRC_TENSOR), 1, B, h3, w3, h3, w3,
                            dL3, L3C, 0, true, st));
     // D_1 (1x1 deconvolution of z)
     SV_TRY_STATUS(mask(dL3, L3C, 0, L3, L3C, 0, 32, p3));
-    SV_TRY_STATUS(wgrad(T_D1, 1, 1, tsrc(Z, 1, ZC, 0, h3, w3, SRC_TENSOR, 0), none, h3, w3, h3, w3, dL3, L3C,
-                        {job(C_D1, 0, false, idc)}, {C_D1}));
+    SV_TRY_STATUS(wgrad(T_D1, C_D1, tsrc(Z, 1, ZC, 0, h3, w3, SRC_TENSOR, 0), none, dL3, L3C));
     SV_TRY_STATUS(tv_dgrad(s, packed, T_D1, fsrc(dL3, 32, L3C, 0, h3, w3, SRC_TENSOR), 1, B, h3, w3, h3, w3,
                            dZ, 1, 0, false, st));
     // Eq. (8), then the head
     hipLaunchKernelGGL(k_tv_reparam_bwd, dim3(cdiv((int)p3, 256)), dim3(256), 0, st, dZ, ML, eps, dms, (int)p3, dML);
     SV_LAUNCH_CHECK("k_tv_reparam_bwd");
-    SV_TRY_STATUS(wgrad(T_MS, 1, 1, tsrc(L3, 48, L3C, 32, h3, w3, SRC_TENSOR, 0), none, h3, w3, h3, w3, dML, DMLC,
-                        {job(C_MS, 0, false, idc)}, {C_MS}));
+    SV_TRY_STATUS(wgrad(T_MS, C_MS, tsrc(L3, 48, L3C, 32, h3, w3, SRC_TENSOR, 0), none, dML, DMLC));
     SV_TRY_STATUS(tv_dgrad(s, packed, T_MS, fsrc(dML, 2, DMLC, 0, h3, w3, SRC_TENSOR), 1, B, h3, w3, h3, w3,
                            dL3, L3C, 32, true, st));
     // EN_2_R
     SV_TRY_STATUS(mask(dL3, L3C, 64, L3, L3C, 64, 16, p3));
-    SV_TRY_STATUS(wgrad(T_EN2R, 5, 1, tsrc(L3, 32, L3C, 32, h3, w3, SRC_TENSOR, 0), none, h3, w3, h3, w3, dL3 + 64, L3C,
-                        {job(C_EN2R, 0, false, idc)}, {C_EN2R}));
+    SV_TRY_STATUS(wgrad(T_EN2R, C_EN2R, tsrc(L3, 32, L3C, 32, h3, w3, SRC_TENSOR, 0), none, dL3 + 64, L3C));
     SV_TRY_STATUS(tv_dgrad(s, packed, T_EN2R, fsrc(dL3, 16, L3C, 64, h3, w3, SRC_TENSOR), 1, B, h3, w3, h3, w3,
                            dL3, L3C, 32, true, st));
     // EN_2 (stride 2: its input gradient runs over the zero-inserted output gradient)
     SV_TRY_STATUS(mask(dL3, L3C, 32, L3, L3C, 32, 32, p3));
-    SV_TRY_STATUS(wgrad(T_EN2, 5, 2, tsrc(L2, 24, L2C, 16, h2, w2, SRC_TENSOR, 0), none, h2, w2, h3, w3, dL3 + 32, L3C,
-                        {job(C_EN2, 0, false, idc)}, {C_EN2}));
+    SV_TRY_STATUS(wgrad(T_EN2, C_EN2, tsrc(L2, 24, L2C, 16, h2, w2, SRC_TENSOR, 0), none, dL3 + 32, L3C));
     SV_TRY_STATUS(tv_dgrad(s, packed, T_EN2, fsrc(dL3, 32, L3C, 32, h3, w3, SRC_ZINS), 1, B, 2 * h3 - 1, 2 * w3 - 1,
                            h2, w2, dL2, L2C, 16, true, st));
     // EN_1_R
     SV_TRY_STATUS(mask(dL2, L2C, 32, L2, L2C, 32, 8, p2));
-    SV_TRY_STATUS(wgrad(T_EN1R, 5, 1, tsrc(L2, 16, L2C, 16, h2, w2, SRC_TENSOR, 0), none, h2, w2, h2, w2, dL2 + 32, L2C,
-                        {job(C_EN1R, 0, false, idc)}, {C_EN1R}));
+    SV_TRY_STATUS(wgrad(T_EN1R, C_EN1R, tsrc(L2, 16, L2C, 16, h2, w2, SRC_TENSOR, 0), none, dL2 + 32, L2C));
     SV_TRY_STATUS(tv_dgrad(s, packed, T_EN1R, fsrc(dL2, 8, L2C, 32, h2, w2, SRC_TENSOR), 1, B, h2, w2, h2, w2,
                            dL2, L2C, 16, true, st));
     // EN_1
     SV_TRY_STATUS(mask(dL2, L2C, 16, L2, L2C, 16, 16, p2));
-    SV_TRY_STATUS(wgrad(T_EN1, 5, 2, tsrc(L1, 64, L1C, 16, h1, w1, SRC_TENSOR, 0), none, h1, w1, h2, w2, dL2 + 16, L2C,
-                        {job(C_EN1, 0, false, idc)}, {C_EN1}));
+    SV_TRY_STATUS(wgrad(T_EN1, C_EN1, tsrc(L1, 64, L1C, 16, h1, w1, SRC_TENSOR, 0), none, dL2 + 16, L2C));
     SV_TRY_STATUS(tv_dgrad(s, packed, T_EN1, fsrc(dL2, 16, L2C, 16, h2, w2, SRC_ZINS), 1, B, 2 * h2 - 1, 2 * w2 - 1,
                            h1, w1, dL1, L1C, 16, true, st));
     // FE_1 (rows 0..31, input channel 0) and FE_2 (rows 32..63, channel 1)
     SV_TRY_STATUS(mask(dL1, L1C, 16, L1, L1C, 16, 64, p1));
-    SV_TRY_STATUS(wgrad(T_FE, 5, 1, x0, none, h1, w1, h1, w1, dL1 + 16, L1C,
-                        {job(C_FE1, 0, false, [](int) { return 0; }), job(C_FE2, 32, false, [](int) { return 1; })},
-                        {C_FE1, C_FE2}));
+    SV_TRY_STATUS(wgrad(T_FE, C_FE1, x0, none, dL1 + 16, L1C));
     return SV_OK;
 }
 

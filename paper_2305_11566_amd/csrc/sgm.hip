@@ -388,81 +388,179 @@ sv_status launch_sgm(const uint64_t *cl, const uint64_t *cr, int B, int h, int w
 // values,
 //   C = 1 - N / sqrt(A B),  N = n SRT - SR ST,  A = n SRR - SR^2,  B = n STT - ST^2,
 // evaluated in FP64 (C = 1 for a flat window, 2 where x - d < 0), and kept as
-// q = floor(32 C + 1/2) in 0..64 for the path aggregation.  One workgroup =
-// ZN_TW x ZN_TH pixels; the reference tile and the target tile (widened by
-// D - 1 columns) with their window halos are staged in LDS; a thread holds its
-// reference window in registers and runs over the disparities.
+// q = floor(32 C + 1/2) in 0..64 for the path aggregation.
+//
+// Bound by integer VALU work.  One workgroup = ZN_TW x ZN_TH pixels, all
+// disparities.  The reference tile and the target tile (widened by the
+// disparities) are kept in LDS as window columns, the 2 RY + 1 bytes above
+// each other packed four to a word, with (SR, 1 / sqrt A) per pixel and
+// (ST, 1 / sqrt B) per target pixel formed once.  A thread takes ZN_K adjacent
+// pixels and four disparities: a column's products are one v_dot4 a word, the
+// window sum SRT slides along the pixels, and lanes run along the disparities
+// of a pixel, so stores are contiguous.  q is decided in FP32 from
+// 32.5 - 32 N / sqrt(A B), whose error is below 2^-15; where that lies within
+// 2^-14 of an integer (about one value in 8000) the thread recomputes the
+// sums and decides in FP64, so every q is the FP64 one.
+// (16 reduced 1242x375 pairs, D = 48, 9 x 7 windows: 41 us; 317 us with three 63-term
+// sums and an FP64 square root and division a value.)
 // ---------------------------------------------------------------------------
-constexpr int ZN_TW = 64, ZN_TH = 4;
+constexpr int ZN_TW = 64, ZN_TH = 4, ZN_K = 8;
+
+// Every sum and product fits 32 bits for windows to 9 x 9: n SRR <= 81 * 81 * 255^2.
+__device__ __forceinline__ int zncc_exact(int n, int SR, int SRR, int ST, int STT, int SRT) {
+    const int N = n * SRT - SR * ST, A = n * SRR - SR * SR, Bv = n * STT - ST * ST;
+    double C;
+    if (A == 0 || Bv == 0) C = 1.0;
+    else C = 1.0 - (double)N / sqrt((double)A * (double)Bv);
+    return (int)floor(32.0 * C + 0.5);
+}
 
 template <int RX, int RY>
-__global__ void __launch_bounds__(ZN_TW * ZN_TH)
+__global__ void __launch_bounds__(256)
 k_zncc_cost(const uint8_t *__restrict__ ll, const uint8_t *__restrict__ lr, int h, int w, int D,
-            int Dp, uint8_t *__restrict__ cost)
+            int Dp, int words, uint8_t *__restrict__ cost)
 {
-    constexpr int PH = ZN_TH + 2 * RY, PWL = ZN_TW + 2 * RX;
-    constexpr int NW = (2 * RX + 1) * (2 * RY + 1);
-    __shared__ uint8_t pr[PH][PWL];
-    __shared__ uint8_t pt[PH][ZN_TW + 2 * RX + 255];
+    constexpr int WY = 2 * RY + 1, NW = (2 * RX + 1) * WY;
+    constexpr int NQ = (WY + 3) / 4;           // words of a window column
+    constexpr int NC = ZN_K + 2 * RX;          // columns of a thread's run
+    constexpr int PWR = ZN_TW + 2 * RX;
+    constexpr int PWT = ZN_TW + 2 * RX + 255;  // at D = 256
+    struct Sum { int s; float r; };            // window sum, 1 / sqrt(n * sum of squares - sum^2) or 0
+    __shared__ __attribute__((aligned(8))) uint32_t cr[ZN_TH][PWR][NQ], ct[ZN_TH][PWT][NQ];
+    __shared__ Sum sr[ZN_TH][ZN_TW], st[ZN_TH][ZN_TW + 255];
     const int b = blockIdx.z;
     const int i0 = blockIdx.y * ZN_TH, j0 = blockIdx.x * ZN_TW;
     const uint8_t *L = ll + (size_t)b * h * w, *R = lr + (size_t)b * h * w;
-    const int PWT = ZN_TW + 2 * RX + D - 1;  // target columns j0 - RX - (D - 1) ...
-    for (int e = threadIdx.x; e < PH * PWL; e += blockDim.x) {
-        const int py = e / PWL, px = e - py * PWL;
-        const int y = min(max(i0 + py - RY, 0), h - 1), x = min(max(j0 + px - RX, 0), w - 1);
-        pr[py][px] = L[(size_t)y * w + x];
-    }
-    for (int e = threadIdx.x; e < PH * PWT; e += blockDim.x) {
-        const int py = e / PWT, px = e - py * PWT;
-        const int y = min(max(i0 + py - RY, 0), h - 1);
-        const int x = min(max(j0 - RX - (D - 1) + px, 0), w - 1);
-        pt[py][px] = R[(size_t)y * w + x];
+    const int nd = (D + 3) / 4, D4 = 4 * nd;
+    const int jt = j0 - (D4 - 1);              // target pixel of st[.][0]; ct[.][0] is RX before it
+    const int nt = ZN_TW + D4 - 1;
+    // window columns, one a thread: its WY + ZN_TH - 1 bytes, then each row's run of WY
+    for (int e = threadIdx.x; e < PWR + nt + 2 * RX; e += 256) {
+        const bool ref = e < PWR;
+        const int c = ref ? e : e - PWR;
+        const int x = min(max((ref ? j0 : jt) - RX + c, 0), w - 1);
+        const uint8_t *img = (ref ? L : R) + x;
+        uint32_t v[WY + ZN_TH - 1];
+#pragma unroll
+        for (int k = 0; k < WY + ZN_TH - 1; ++k) v[k] = img[(size_t)min(max(i0 + k - RY, 0), h - 1) * w];
+#pragma unroll
+        for (int y = 0; y < ZN_TH; ++y)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                uint32_t word = 0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (4 * q + k < WY) word |= v[y + 4 * q + k] << (8 * k);
+                if (ref) cr[y][c][q] = word;
+                else ct[y][c][q] = word;
+            }
     }
     __syncthreads();
-    const int ty = threadIdx.x / ZN_TW, tx = threadIdx.x - ty * ZN_TW;
-    const int i = i0 + ty, j = j0 + tx;
-    if (i >= h || j >= w) return;
-    int rv[NW];
-    int SR = 0, SRR = 0;
+    for (int e = threadIdx.x; e < ZN_TH * (ZN_TW + nt); e += 256) {
+        const int y = e / (ZN_TW + nt), c = e - y * (ZN_TW + nt);
+        const bool ref = c < ZN_TW;
+        uint32_t s = 0, ss = 0;
 #pragma unroll
-    for (int dy = 0; dy <= 2 * RY; ++dy)
+        for (int dx = 0; dx <= 2 * RX; ++dx)
 #pragma unroll
-        for (int dx = 0; dx <= 2 * RX; ++dx) {
-            const int r = pr[ty + dy][tx + dx];
-            rv[dy * (2 * RX + 1) + dx] = r;
-            SR += r;
-            SRR += r * r;
+            for (int q = 0; q < NQ; ++q) {
+                const uint32_t v = ref ? cr[y][c + dx][q] : ct[y][c - ZN_TW + dx][q];
+                s = __builtin_amdgcn_udot4(v, 0x01010101u, s, false);
+                ss = __builtin_amdgcn_udot4(v, v, ss, false);
+            }
+        const int var = NW * (int)ss - (int)s * (int)s;
+        const Sum r = {(int)s, var > 0 ? __builtin_amdgcn_rsqf((float)var) : 0.f};
+        if (ref) sr[y][c] = r;
+        else st[y][c - ZN_TW] = r;
+    }
+    __syncthreads();
+    constexpr int NRUN = ZN_TW / ZN_K;
+    for (int item = threadIdx.x; item < ZN_TH * NRUN * nd; item += 256) {
+        const int db = item % nd, pr = item / nd;
+        const int y = pr / NRUN, x = (pr - y * NRUN) * ZN_K;
+        const int i = i0 + y, j = j0 + x, d0 = 4 * db;
+        if (i >= h || j >= w) continue;
+        // column c of the run against disparity d0 + q is target column c - q + 3 of tc
+        uint32_t rc[NC][NQ], tc[NC + 3][NQ];
+        const int t0 = x + (D4 - 1) - d0 - 3;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int k = 0; k < NQ; ++k) rc[c][k] = cr[y][x + c][k];
+#pragma unroll
+        for (int c = 0; c < NC + 3; ++c)
+#pragma unroll
+            for (int k = 0; k < NQ; ++k) tc[c][k] = ct[y][t0 + c][k];
+        Sum a[ZN_K], t[ZN_K + 3];
+#pragma unroll
+        for (int k = 0; k < ZN_K; ++k) {
+            a[k] = sr[y][x + k];
+            a[k].r *= 32.0f;
         }
-    const long long n = NW;
-    const long long A = n * SRR - (long long)SR * SR;
-    uint8_t *o = cost + (((size_t)b * h + i) * w + j) * Dp;
-    for (int d = 0; d < Dp; ++d) {
-        int q = 0;
-        if (d < D) {
-            if (j - d < 0) {
-                q = 64;
-            } else {
-                // target window of column j - d: pt column tx + dx + (D - 1) - d
-                int ST = 0, STT = 0, SRT = 0;
 #pragma unroll
-                for (int dy = 0; dy <= 2 * RY; ++dy)
+        for (int k = 0; k < ZN_K + 3; ++k) t[k] = st[y][t0 + k];
+        uint32_t out[ZN_K], near = 0;
 #pragma unroll
-                    for (int dx = 0; dx <= 2 * RX; ++dx) {
-                        const int t = pt[ty + dy][tx + dx + (D - 1) - d];
-                        ST += t;
-                        STT += t * t;
-                        SRT += rv[dy * (2 * RX + 1) + dx] * t;
-                    }
-                const long long N = n * SRT - (long long)SR * ST;
-                const long long Bv = n * STT - (long long)ST * ST;
-                double C;
-                if (A == 0 || Bv == 0) C = 1.0;
-                else C = 1.0 - (double)N / sqrt((double)A * (double)Bv);
-                q = (int)floor(32.0 * C + 0.5);
+        for (int k = 0; k < ZN_K; ++k) out[k] = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int d = d0 + q;
+            uint32_t P[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                P[c] = 0;
+#pragma unroll
+                for (int k = 0; k < NQ; ++k) P[c] = __builtin_amdgcn_udot4(rc[c][k], tc[c - q + 3][k], P[c], false);
+            }
+            uint32_t S = 0;
+#pragma unroll
+            for (int c = 0; c < 2 * RX + 1; ++c) S += P[c];
+#pragma unroll
+            for (int k = 0; k < ZN_K; ++k) {
+                if (k) S += P[k + 2 * RX] - P[k - 1];
+                const Sum tk = t[k - q + 3];
+                // factors below 2^24: full-rate multiplies
+                const int N = (int)__umul24(S, NW) - (int)__umul24(a[k].s, tk.s);
+                const float v = fmaf(-(float)N, a[k].r * tk.r, 32.5f);
+                const float fl = floorf(v);
+                uint32_t qv = (uint32_t)(int)fl;
+                const bool out_left = j + k < d;
+                if (out_left) qv = 64;
+                if (d >= D) qv = 0;
+                out[k] |= qv << (8 * q);
+                // v - fl in [2^-14, 1 - 2^-14]: the FP64 expression has the same floor
+                if (fabsf(v - fl - 0.5f) > 0.5f - 0x1p-14f && !out_left) near |= 1u << (8 * q + k);
             }
         }
-        o[d] = (uint8_t)q;
+        while (near) {
+            const int bit = __ffs(near) - 1;
+            near &= near - 1;
+            const int q = bit >> 3, k = bit & 7;
+            if (d0 + q >= D) continue;
+            int SRR = 0, STT = 0, SRT = 0;
+            for (int dx = 0; dx <= 2 * RX; ++dx)
+                for (int m = 0; m < NQ; ++m) {
+                    const uint32_t rv = cr[y][x + k + dx][m], tv = ct[y][t0 + k - q + 3 + dx][m];
+                    SRR = (int)__builtin_amdgcn_udot4(rv, rv, (uint32_t)SRR, false);
+                    STT = (int)__builtin_amdgcn_udot4(tv, tv, (uint32_t)STT, false);
+                    SRT = (int)__builtin_amdgcn_udot4(rv, tv, (uint32_t)SRT, false);
+                }
+            const uint32_t v = (uint32_t)zncc_exact(NW, sr[y][x + k].s, SRR, st[y][t0 + k - q + 3].s, STT, SRT);
+#pragma unroll
+            for (int kk = 0; kk < ZN_K; ++kk)
+                if (kk == k) out[kk] = (out[kk] & ~(0xffu << (8 * q))) | (v << (8 * q));
+        }
+        uint8_t *o = cost + (((size_t)b * h + i) * w + j) * Dp + d0;
+#pragma unroll
+        for (int k = 0; k < ZN_K; ++k) {
+            if (j + k >= w) break;
+            if (words) {
+                *(uint32_t *)(o + (size_t)k * Dp) = out[k];
+            } else {
+                for (int q = 0; q < 4; ++q)
+                    if (d0 + q < Dp) o[(size_t)k * Dp + q] = (uint8_t)(out[k] >> (8 * q));
+            }
+        }
     }
 }
 
@@ -478,10 +576,11 @@ sv_status launch_zncc_cost(const uint8_t *ll, const uint8_t *lr, int B, int h, i
 {
     const dim3 grid(cdiv(w, ZN_TW), cdiv(h, ZN_TH), B);
     const int rx = (win_w - 1) / 2, ry = (win_h - 1) / 2;
+    // four disparities as one word where every pixel's row of costs is aligned
+    const int words = Dp % 4 == 0 && (uintptr_t)cost % 4 == 0;
 #define SV_ZN(X, Y)                                                                                \
     if (rx == X && ry == Y) {                                                                      \
-        hipLaunchKernelGGL((k_zncc_cost<X, Y>), grid, dim3(ZN_TW * ZN_TH), 0, s, ll, lr, h, w, D, Dp, \
-                           cost);                                                                  \
+        hipLaunchKernelGGL((k_zncc_cost<X, Y>), grid, dim3(256), 0, s, ll, lr, h, w, D, Dp, words, cost); \
         SV_LAUNCH_CHECK("k_zncc_cost");                                                            \
         return SV_OK;                                                                              \
     }

@@ -117,3 +117,22 @@ def test_zncc_unsupported_window_is_an_error():
     ll = cuda(np.zeros((1, 8, 8), np.uint8))
     with pytest.raises(sv.SvError):
         sv.sv_zncc_cost(ll, ll, 4, 11, 3)
+
+
+@pytest.mark.parametrize("ww,wh", [(3, 3), (5, 5), (7, 7), (9, 7), (7, 9), (9, 9), (5, 3), (3, 5)])
+@pytest.mark.parametrize("h,w,D", [(5, 67, 6), (4, 64, 48), (3, 9, 1), (9, 130, 77)])
+def test_zncc_windows_and_ragged_runs(ww, wh, h, w, D):
+    """Every window the kernel has, at widths around its 64-pixel tiles and
+    8-pixel runs and disparity ranges around its groups of four, with values
+    from few levels so that flat windows and costs on a rounding boundary occur."""
+    import paper_2305_11566_amd as sv
+    rng = np.random.default_rng(h * 1000 + w + ww)
+    ll = (rng.integers(0, 3, (2, h, w)) * 60 + 5).astype(np.uint8)
+    lr = np.where(rng.random((2, h, w)) < 0.2, 255 - ll, np.roll(ll, -1, axis=2)).astype(np.uint8)
+    lr[1] = 7
+    c = sv.sv_zncc_cost(cuda(ll), cuda(lr), D, ww, wh)
+    raw = sv.sv_zncc_sgm(cuda(ll), cuda(lr), D, ww, wh, 10, 120)
+    torch.cuda.synchronize()
+    ref = oracle.zncc_cost(ll, lr, D, ww, wh)
+    assert (c.cpu().numpy().astype(np.int32) == ref).all()
+    assert (raw.cpu().numpy() == oracle.wta(oracle.sgm(ref, 10, 120))).all()

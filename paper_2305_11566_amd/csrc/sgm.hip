@@ -20,16 +20,18 @@ namespace sv {
 constexpr int SGM_INF = 0x3fff;        // above any path cost (uint8 range)
 constexpr int SGM_LANES = 16;          // lanes per path = one DPP row
 
+// A lane's value of another lane of its DPP row; `old` where there is none.
 template <int CTRL>
-__device__ __forceinline__ int dpp(int old, int v) {
-    return __builtin_amdgcn_update_dpp(old, v, CTRL, 0xf, 0xf, false);
+__device__ __forceinline__ uint32_t dpp(uint32_t old, uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, 0xf, 0xf, false);
 }
-// min over the 16 lanes of a DPP row, in every lane of the row
-__device__ __forceinline__ int row_min(int v) {
-    v = min(v, dpp<0x121>(0, v));  // row_ror:1
-    v = min(v, dpp<0x122>(0, v));  // row_ror:2
-    v = min(v, dpp<0x124>(0, v));  // row_ror:4
-    v = min(v, dpp<0x128>(0, v));  // row_ror:8
+// min over the 16 lanes of a DPP row, in every lane of the row (a rotation has
+// no lane without a source, so each step is one v_min with a DPP operand)
+__device__ __forceinline__ uint32_t row_min(uint32_t v) {
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x121, 0xf, 0xf, true));  // row_ror:1
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x122, 0xf, 0xf, true));  // row_ror:2
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x124, 0xf, 0xf, true));  // row_ror:4
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x128, 0xf, 0xf, true));  // row_ror:8
     return v;
 }
 
@@ -75,39 +77,32 @@ k_sgm_cost(const uint64_t *__restrict__ cl, const uint64_t *__restrict__ cr, int
 
 // Path p of npath: directions 0 (left to right) and 1 (right to left) run
 // along rows, 2 (top to bottom) and 3 (bottom to top) along columns;
-// vol[dir][b][y][x][Dp].  The step's costs are loaded SGM_PF steps ahead into
-// a ring of registers, so the dependent chain of a step is arithmetic and DPP
-// only.
+// vol[dir][b][y][x][Dp].
+//
+// Bound by the dependent instructions of one wave's chain of w steps at small
+// batches and by the volumes' traffic at large ones.  A lane holds its DPL path
+// costs two to a register (16-bit halves, packed min and add).  With mn the
+// minimum of the previous pixel, cur = min(prev, left + P1, right + P1,
+// mn + P2) + (c - mn): the row minimum is needed for two of the operands only,
+// and the neighbours' terms are formed beside it.  A path starts from prev =
+// mn = 0, which gives cur = c.  Disparities past D get SGM_INF or'ed into
+// their cost; they stay above every valid cost + P1 and never win.  Costs are
+// loaded a block of SGM_PF steps ahead into one of two sets of registers, each
+// used in place (a single set made the compiler copy it, and wait for the last
+// store, at every block, and loads under a branch made every step of a path's
+// tail wait for memory).  Pointers advance by a stride; lanes past Dp read a
+// fixed cost and all write one word of the sink by a stride of 0, without a
+// test (a word of the sink for each of them costs a request each: 121 us below
+// instead of 44).
+// (At 1/4 of 1242x375, D = 48, one pair / 16 pairs: 28 / 45 us; 58 / 122 us
+// with one value a register, selects on every access and a sink word a lane.)
 constexpr int SGM_PF = 16;
-template <int DPL>
-struct CostWords {
-    static constexpr int N = DPL >= 4 ? DPL / 4 : 1;
-    uint32_t v[N];
-    uint32_t ok;  // bit k: word k holds costs (else it is read as zero)
-};
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 
-// The costs of disparities d0 .. d0 + DPL - 1 of one pixel (p points at d0).
-// The loads are unconditional (a word at or past Dp, or of a step past the
-// path's end, reads `safe` instead) and the mask is applied where the costs
-// are used, so nothing waits for a load until its step comes.
-template <int DPL>
-__device__ __forceinline__ void load_costs(const uint8_t *__restrict__ p, const uint8_t *safe, bool ok,
-                                           int d0, int Dp, CostWords<DPL> &c) {
-    c.ok = 0;
-    if constexpr (DPL >= 4) {
-#pragma unroll
-        for (int k = 0; k < DPL / 4; ++k) {
-            const bool okk = ok && d0 + 4 * k < Dp;
-            c.v[k] = *(const uint32_t *)(okk ? p + 4 * k : safe);
-            c.ok |= (uint32_t)okk << k;
-        }
-    } else if constexpr (DPL == 2) {
-        c.v[0] = *(const uint16_t *)(ok ? p : safe);
-        c.ok = ok;
-    } else {
-        c.v[0] = *(ok ? p : safe);
-        c.ok = ok;
-    }
+// (lo's high half, hi's low half)
+__device__ __forceinline__ u16x2 mid2(u16x2 hi, u16x2 lo) {
+    return __builtin_bit_cast(u16x2, __builtin_amdgcn_alignbit(__builtin_bit_cast(uint32_t, hi),
+                                                               __builtin_bit_cast(uint32_t, lo), 16));
 }
 
 template <int DPL>
@@ -115,6 +110,8 @@ __global__ void __launch_bounds__(64)
 k_sgm_paths(const uint8_t *__restrict__ cost, int B, int h, int w, int D, int Dp, int P1, int P2,
             uint8_t *__restrict__ vol, uint8_t *__restrict__ sink)
 {
+    constexpr int NR = DPL / 2;                    // registers of path costs
+    constexpr int NWD = DPL >= 4 ? DPL / 4 : 1;    // words of costs (DPL = 2: a half word)
     const int lane = threadIdx.x & (SGM_LANES - 1);
     const int path = blockIdx.x * 4 + (threadIdx.x >> 4);
     const int nrow = B * h, ncol = B * w;
@@ -139,145 +136,225 @@ k_sgm_paths(const uint8_t *__restrict__ cost, int B, int h, int w, int D, int Dp
     const uint8_t *cb = cost + (size_t)b * plane * Dp;
     uint8_t *vb = vol + ((size_t)dir * B + b) * plane * Dp;
     const int d0 = lane * DPL;
-    const bool lane_ok = d0 < Dp;
-    // pixel offset (in pixels) of step s
-    const long long step_px = (long long)dy * w + dx;
-    const long long px0 = (long long)y0 * w + x0;
-    // words of lanes past Dp are stored to a per-lane sink (never read), so
-    // stores, like loads, need no branch
-    uint8_t *my_sink = sink + (size_t)(threadIdx.x & 63) * 64;
-
-    CostWords<DPL> ring[SGM_PF];
+    const long long step = ((long long)dy * w + dx) * Dp, at0 = ((long long)y0 * w + x0) * Dp;
+    // per word: where it is read and written; a word past Dp reads the first
+    // costs of the image and writes this lane's slot of the sink
+    const uint8_t *lp[NWD];
+    uint8_t *sp[NWD];
+    long long st[NWD];
+    bool ok[NWD];
+    uint32_t pad[NR];  // SGM_INF in the halves whose disparity is past D
 #pragma unroll
-    for (int k = 0; k < SGM_PF; ++k)
-        load_costs<DPL>(cb + (size_t)(px0 + (long long)(k < len ? k : 0) * step_px) * Dp + d0, cb,
-                        lane_ok && k < len, d0, Dp, ring[k]);
-
-    int prev[DPL];
-#pragma unroll
-    for (int j = 0; j < DPL; ++j) prev[j] = SGM_INF;
-    int mprev = 0;
-    // one step s of the path, its costs in ring slot k (refilled with step s + SGM_PF)
-    auto step = [&](int k, int s) {
-        int c[DPL];
-#pragma unroll
-        for (int j = 0; j < DPL; ++j) {
-            const int q = DPL >= 4 ? j / 4 : 0;
-            const uint32_t word = ((ring[k].ok >> q) & 1u) ? ring[k].v[q] : 0u;
-            const int sh = DPL >= 4 ? 8 * (j % 4) : 8 * j;
-            c[j] = d0 + j < D ? (int)((word >> sh) & 0xffu) : SGM_INF;
-        }
-        const int sn = s + SGM_PF;
-        load_costs<DPL>(cb + (size_t)(px0 + (long long)(sn < len ? sn : 0) * step_px) * Dp + d0, cb,
-                        lane_ok && sn < len, d0, Dp, ring[k]);
-        int cur[DPL];
-        if (s == 0) {
-#pragma unroll
-            for (int j = 0; j < DPL; ++j) cur[j] = c[j];
-        } else {
-            const int from_left = dpp<0x111>(SGM_INF, prev[DPL - 1]);  // row_shr:1: lane - 1
-            const int from_right = dpp<0x101>(SGM_INF, prev[0]);       // row_shl:1: lane + 1
-#pragma unroll
-            for (int j = 0; j < DPL; ++j) {
-                const int lft = j > 0 ? prev[j - 1] : from_left;
-                const int rgt = j + 1 < DPL ? prev[j + 1] : from_right;
-                int m = min(prev[j], min(lft, rgt) + P1);
-                m = min(m, mprev + P2);
-                cur[j] = c[j] >= SGM_INF ? SGM_INF : c[j] + m - mprev;
-            }
-        }
-        int mn = cur[0];
-#pragma unroll
-        for (int j = 1; j < DPL; ++j) mn = min(mn, cur[j]);
-        mprev = row_min(mn);
-        uint8_t *o = vb + (size_t)(px0 + (long long)s * step_px) * Dp + d0;
-        if constexpr (DPL >= 4) {
-#pragma unroll
-            for (int q = 0; q < DPL / 4; ++q) {
-                uint32_t word = 0;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) word |= (uint32_t)(cur[4 * q + t] & 0xff) << (8 * t);
-                const bool okq = lane_ok && d0 + 4 * q < Dp;
-                *(uint32_t *)(okq ? o + 4 * q : my_sink + 4 * q) = word;
-            }
-        } else if constexpr (DPL == 2) {
-            *(uint16_t *)(lane_ok ? o : my_sink) = (uint16_t)((cur[0] & 0xff) | ((cur[1] & 0xff) << 8));
-        } else {
-            *(lane_ok ? o : my_sink) = (uint8_t)cur[0];
-        }
-#pragma unroll
-        for (int j = 0; j < DPL; ++j) prev[j] = cur[j];
-    };
-    int s0 = 0;
-    for (; s0 + SGM_PF <= len; s0 += SGM_PF) {
-#pragma unroll
-        for (int k = 0; k < SGM_PF; ++k) step(k, s0 + k);
+    for (int k = 0; k < NWD; ++k) {
+        ok[k] = d0 + 4 * k < Dp;
+        lp[k] = ok[k] ? cb + at0 + d0 + 4 * k : cb;
+        sp[k] = ok[k] ? vb + at0 + d0 + 4 * k : sink + (blockIdx.x & 63) * 64;
+        st[k] = ok[k] ? step : 0;
     }
 #pragma unroll
-    for (int k = 0; k < SGM_PF; ++k)
-        if (s0 + k < len) step(k, s0 + k);
+    for (int r = 0; r < NR; ++r)
+        pad[r] = (d0 + 2 * r < D ? 0u : (uint32_t)SGM_INF) | (d0 + 2 * r + 1 < D ? 0u : (uint32_t)SGM_INF << 16);
+
+    // the costs of the SGM_PF steps from s on; past the path's end (guard) the
+    // last step's again, so that loads are unconditional
+    auto fetch = [&](uint32_t (&c)[SGM_PF][NWD], int s, bool guard) {
+#pragma unroll
+        for (int k = 0; k < SGM_PF; ++k) {
+            const bool adv = !guard || s + k + 1 < len;
+#pragma unroll
+            for (int q = 0; q < NWD; ++q) {
+                if constexpr (DPL == 2) c[k][q] = *(const uint16_t *)lp[q];
+                else c[k][q] = *(const uint32_t *)lp[q];
+                lp[q] += adv ? st[q] : 0;
+            }
+        }
+    };
+    u16x2 prev[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) prev[r] = u16x2{0, 0};
+    u16x2 mn = {0, 0};  // the minimum of the previous pixel's path costs, twice
+    const u16x2 p1 = {(uint16_t)P1, (uint16_t)P1}, p2 = {(uint16_t)P2, (uint16_t)P2};
+
+    // one step with the costs cw
+    auto run = [&](const uint32_t (&cw)[NWD]) {
+        u16x2 c[NR];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            // bytes 2 r and 2 r + 1 of the costs as 16-bit halves
+            const uint32_t h2 = __builtin_amdgcn_perm(0u, cw[r / 2], (r & 1) ? 0x0c030c02u : 0x0c010c00u);
+            c[r] = __builtin_bit_cast(u16x2, h2 | pad[r]);
+        }
+        // lane - 1's last and lane + 1's first register, SGM_INF at the row's ends
+        const u16x2 from_l = __builtin_bit_cast(u16x2, dpp<0x111>((uint32_t)SGM_INF << 16,
+                                                                  __builtin_bit_cast(uint32_t, prev[NR - 1])));
+        const u16x2 from_r = __builtin_bit_cast(u16x2, dpp<0x101>((uint32_t)SGM_INF,
+                                                                  __builtin_bit_cast(uint32_t, prev[0])));
+        u16x2 x[NR + 1];  // x[r] = (cost 2 r - 1, cost 2 r)
+        x[0] = mid2(prev[0], from_l);
+#pragma unroll
+        for (int r = 1; r < NR; ++r) x[r] = mid2(prev[r], prev[r - 1]);
+        x[NR] = mid2(from_r, prev[NR - 1]);
+        u16x2 cur[NR];
+        const u16x2 q = p2 + mn;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            u16x2 m = __builtin_elementwise_min(x[r], x[r + 1]) + p1;
+            m = __builtin_elementwise_min(m, prev[r]);
+            cur[r] = __builtin_elementwise_min(m, q) + (c[r] - mn);
+        }
+        u16x2 t = cur[0];
+#pragma unroll
+        for (int r = 1; r < NR; ++r) t = __builtin_elementwise_min(t, cur[r]);
+        const uint32_t least = row_min(min((uint32_t)t[0], (uint32_t)t[1]));
+#pragma unroll
+        for (int k = 0; k < NWD; ++k) {
+            if constexpr (DPL == 2) {
+                *(uint16_t *)sp[k] = (uint16_t)__builtin_amdgcn_perm(0u, __builtin_bit_cast(uint32_t, cur[0]), 0x0c0c0200u);
+            } else {
+                *(uint32_t *)sp[k] = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, cur[2 * k + 1]),
+                                                           __builtin_bit_cast(uint32_t, cur[2 * k]), 0x06040200u);
+            }
+            sp[k] += st[k];
+        }
+        mn = u16x2{(uint16_t)least, (uint16_t)least};
+#pragma unroll
+        for (int r = 0; r < NR; ++r) prev[r] = cur[r];
+    };
+    auto full = [&](const uint32_t (&c)[SGM_PF][NWD]) {
+#pragma unroll
+        for (int k = 0; k < SGM_PF; ++k) run(c[k]);
+    };
+    auto part = [&](const uint32_t (&c)[SGM_PF][NWD], int s) {
+#pragma unroll
+        for (int k = 0; k < SGM_PF; ++k)
+            if (s + k < len) run(c[k]);
+    };
+    uint32_t ra[SGM_PF][NWD], rb[SGM_PF][NWD];
+    fetch(ra, 0, true);
+    int s = 0;
+    for (; s + 3 * SGM_PF < len; s += 2 * SGM_PF) {  // both blocks and the next are on the path
+        fetch(rb, s + SGM_PF, false);
+        full(ra);
+        fetch(ra, s + 2 * SGM_PF, false);
+        full(rb);
+    }
+    fetch(rb, s + SGM_PF, true);
+    part(ra, s);
+    fetch(ra, s + 2 * SGM_PF, true);
+    part(rb, s + SGM_PF);
+    part(ra, s + 2 * SGM_PF);
 }
 
 // Aggregated cost (Eq. (5)) and winner-take-all (Eq. (6)), lowest d on ties;
-// the four volumes are [B][h][w][Dp].
+// the four volumes are [B][h][w][Dp].  Bound by reading the four volumes: a
+// thread takes CW words (4 CW disparities) of one pixel, so a wave reads
+// contiguous memory, keeps the least key (sum << 8 | d), and a pixel's nch
+// threads meet in LDS.  CW = 4 (16-byte loads) where Dp is a multiple of 16.
+// (16 reduced 1242x375 pairs, D = 48: 16 us; 59 us with a thread a pixel, each lane
+// reading a row of its own.)
+template <int CW>
 __global__ void __launch_bounds__(256)
-k_sgm_wta(const uint8_t *__restrict__ vol, size_t nvox, int D, int Dp, size_t npix,
+k_sgm_wta(const uint8_t *__restrict__ vol, size_t nvox, int D, int Dp, int nch, size_t npix,
           uint8_t *__restrict__ disp)
 {
-    for (size_t p = blockIdx.x * (size_t)blockDim.x + threadIdx.x; p < npix;
-         p += (size_t)gridDim.x * blockDim.x) {
-        const uint8_t *v0 = vol + p * Dp, *v1 = v0 + nvox, *v2 = v1 + nvox, *v3 = v2 + nvox;
-        int best = 0x7fffffff, bd = 0;
-        for (int d = 0; d < D; d += 4) {
-            const uint32_t a = *(const uint32_t *)(v0 + d), bq = *(const uint32_t *)(v1 + d);
-            const uint32_t cq = *(const uint32_t *)(v2 + d), dq = *(const uint32_t *)(v3 + d);
+    typedef uint32_t words __attribute__((ext_vector_type(CW)));
+    __shared__ uint32_t key[256];
+    const int per = 256 / nch;  // pixels of a workgroup
+    const int pl = threadIdx.x / nch, ch = threadIdx.x - pl * nch;
+    for (size_t p0 = (size_t)blockIdx.x * per; p0 < npix; p0 += (size_t)gridDim.x * per) {
+        uint32_t best = 0xffffffffu;
+        if (pl < per && p0 + pl < npix) {
+            const uint8_t *v = vol + (p0 + pl) * Dp + 4 * CW * ch;
+            words q[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int sh = 8 * k;
-                const int s = (int)((a >> sh) & 0xff) + (int)((bq >> sh) & 0xff) +
-                              (int)((cq >> sh) & 0xff) + (int)((dq >> sh) & 0xff);
-                if (d + k < D && s < best) { best = s; bd = d + k; }
+            for (int r = 0; r < 4; ++r) q[r] = *(const words *)(v + r * nvox);
+#pragma unroll
+            for (int k = 0; k < CW; ++k) {
+                uint32_t even = 0, odd = 0;  // sums of bytes 0, 2 and of bytes 1, 3 as 16-bit halves
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const uint32_t u = CW == 1 ? ((const uint32_t *)&q[r])[0] : q[r][k];
+                    even += u & 0x00ff00ffu;
+                    odd += (u >> 8) & 0x00ff00ffu;
+                }
+                const int d = 4 * (CW * ch + k);
+                if (d < D) best = min(best, (even & 0xffffu) << 8 | (uint32_t)d);
+                if (d + 1 < D) best = min(best, (odd & 0xffffu) << 8 | (uint32_t)(d + 1));
+                if (d + 2 < D) best = min(best, (even >> 16) << 8 | (uint32_t)(d + 2));
+                if (d + 3 < D) best = min(best, (odd >> 16) << 8 | (uint32_t)(d + 3));
             }
         }
-        disp[p] = (uint8_t)bd;
+        key[threadIdx.x] = best;
+        __syncthreads();
+        if ((int)threadIdx.x < per && p0 + threadIdx.x < npix) {
+            uint32_t m = key[threadIdx.x * nch];
+            for (int k = 1; k < nch; ++k) m = min(m, key[threadIdx.x * nch + k]);
+            disp[p0 + threadIdx.x] = (uint8_t)(m & 0xffu);
+        }
+        __syncthreads();
     }
 }
 
-// Single matching phase (Eq. (7)) with nearest-valid filling, one wave per
-// row.  The target column of x is x - D(x); x is invalid when a pixel x + k,
-// 0 < k < D, has the same target column (the left pixel of such a pair is
-// the one hidden in the target view).  Validity is kept as one 64-bit ballot
+// Single matching phase (Eq. (7)) with nearest-valid filling, one workgroup
+// per row.  The target column of x is x - D(x); x is invalid when a pixel
+// x + k, 0 < k < D, has the same target column (the left pixel of such a pair
+// is the one hidden in the target view).  Validity is kept as one 64-bit ballot
 // per 64 pixels; each invalid pixel takes the nearest valid value of its row
 // (the smaller one at equal distances).  The row is staged in LDS.
+//
+// Two pixels with one target column are apart by the difference of their
+// disparities, which is below D when every disparity of the row is.  Then x is
+// valid exactly when it is the last pixel with its target column, and the
+// kernel finds those with one LDS maximum a pixel instead of a search over D
+// pixels.  A row with a disparity of D or more, and rows too wide for the table
+// in LDS (use_last = 0), are searched.
+// (94 rows of 311 pixels, D = 48: 5 us; 29 us with one wave a row and the search.)
 constexpr int SMP_MAXW = 16384;
-__global__ void __launch_bounds__(64)
-k_smp(const uint8_t *__restrict__ disp, int B, int h, int w, int D, uint8_t *__restrict__ out)
+constexpr int SMP_LASTW = 8192;  // widest row with the table: 41 KB of LDS
+__global__ void __launch_bounds__(256)
+k_smp(const uint8_t *__restrict__ disp, int w, int D, int use_last, uint8_t *__restrict__ out)
 {
-    __shared__ uint8_t row[SMP_MAXW];
-    __shared__ uint64_t valid[SMP_MAXW / 64];
-    const int lane = threadIdx.x;
-    const size_t base = (size_t)blockIdx.x * w;  // row blockIdx.x of B * h
-    for (int x = lane; x < w; x += 64) row[x] = disp[base + x];
-    __syncthreads();
+    extern __shared__ __attribute__((aligned(16))) char smem[];
     const int nch = (w + 63) / 64;
-    for (int ch = 0; ch < nch; ++ch) {
+    uint64_t *valid = (uint64_t *)smem;
+    uint8_t *row = (uint8_t *)(valid + nch);
+    int *last = (int *)(row + ((w + 3) & ~3));  // [w + 255]: last pixel with target column t - 255
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const size_t base = (size_t)blockIdx.x * w;  // row blockIdx.x of B * h
+    bool big = false;
+    for (int x = tid; x < w; x += 256) {
+        const int d = disp[base + x];
+        row[x] = (uint8_t)d;
+        big |= d >= D;
+    }
+    if (use_last)
+        for (int x = tid; x < w + 255; x += 256) last[x] = -1;
+    const bool search = __syncthreads_or(big) || !use_last;
+    if (!search) {
+        for (int x = tid; x < w; x += 256) atomicMax(&last[x - row[x] + 255], x);
+        __syncthreads();
+    }
+    for (int ch = wave; ch < nch; ch += 4) {
         const int x = ch * 64 + lane;
         bool ok = x < w;
         if (ok) {
             const int t = x - row[x];
-            for (int k = 1; k < D && x + k < w; ++k)
-                if (x + k - row[x + k] == t) { ok = false; break; }
+            if (!search) {
+                ok = last[t + 255] == x;
+            } else {
+                for (int k = 1; k < D && x + k < w; ++k)
+                    if (x + k - row[x + k] == t) { ok = false; break; }
+            }
         }
         const uint64_t m = __ballot(ok);
         if (lane == 0) valid[ch] = m;
     }
     __syncthreads();
-    bool any = false;
-    for (int ch = 0; ch < nch; ++ch) any |= valid[ch] != 0;
-    for (int x = lane; x < w; x += 64) {
+    // (the last pixel of a row is always valid)
+    for (int x = tid; x < w; x += 256) {
         const int ch = x >> 6, bit = x & 63;
         uint8_t v = row[x];
-        if (any && !((valid[ch] >> bit) & 1)) {
+        if (!((valid[ch] >> bit) & 1)) {
             // nearest valid index below x and above x (-1 / w when none)
             int lo = -1, hi = w;
             uint64_t mb = valid[ch] & ((bit ? (~0ull >> (64 - bit)) : 0ull));
@@ -357,16 +434,18 @@ static sv_status sgm_from_cost(int B, int h, int w, int D, int P1, int P2, uint8
     const int dpl = cdiv(D, SGM_LANES);
 #define SV_SGM(N) \
     hipLaunchKernelGGL(k_sgm_paths<N>, grid, dim3(64), 0, s, cost, B, h, w, D, Dp, P1, P2, vol, sink)
-    if (dpl <= 1) SV_SGM(1);
-    else if (dpl <= 2) SV_SGM(2);
+    if (dpl <= 2) SV_SGM(2);
     else if (dpl <= 4) SV_SGM(4);
     else if (dpl <= 8) SV_SGM(8);
     else SV_SGM(16);
 #undef SV_SGM
     SV_LAUNCH_CHECK("k_sgm_paths");
     const size_t npix = (size_t)B * h * w;
-    const int blocks = (int)std::min<size_t>((npix + 255) / 256, 8192);
-    hipLaunchKernelGGL(k_sgm_wta, dim3(blocks), dim3(256), 0, s, vol, nvox, D, Dp, npix, disp);
+    const bool wide = Dp % 16 == 0 && (uintptr_t)ws % 16 == 0;
+    const int nch = Dp / (wide ? 16 : 4);
+    const int blocks = (int)std::min<size_t>((npix + 256 / nch - 1) / (256 / nch), 16384);
+    if (wide) hipLaunchKernelGGL(k_sgm_wta<4>, dim3(blocks), dim3(256), 0, s, vol, nvox, D, Dp, nch, npix, disp);
+    else hipLaunchKernelGGL(k_sgm_wta<1>, dim3(blocks), dim3(256), 0, s, vol, nvox, D, Dp, nch, npix, disp);
     SV_LAUNCH_CHECK("k_sgm_wta");
     return SV_OK;
 }
@@ -601,7 +680,9 @@ sv_status launch_smp_median(const uint8_t *disp, int B, int h, int w, int D, uin
                             uint8_t *out, hipStream_t s)
 {
     if (w > SMP_MAXW) return SV_ERR_SHAPE;
-    hipLaunchKernelGGL(k_smp, dim3(B * h), dim3(64), 0, s, disp, B, h, w, D, tmp);
+    const int use_last = w <= SMP_LASTW;
+    const size_t lds = (size_t)cdiv(w, 64) * 8 + ((w + 3) & ~3) + (use_last ? (size_t)(w + 255) * 4 : 0);
+    hipLaunchKernelGGL(k_smp, dim3(B * h), dim3(256), lds, s, disp, w, D, use_last, tmp);
     SV_LAUNCH_CHECK("k_smp");
     const size_t n = (size_t)B * h * w;
     const int blocks = (int)std::min<size_t>((n + 255) / 256, 8192);

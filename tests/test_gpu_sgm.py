@@ -136,3 +136,35 @@ def test_zncc_windows_and_ragged_runs(ww, wh, h, w, D):
     ref = oracle.zncc_cost(ll, lr, D, ww, wh)
     assert (c.cpu().numpy().astype(np.int32) == ref).all()
     assert (raw.cpu().numpy() == oracle.wta(oracle.sgm(ref, 10, 120))).all()
+
+
+@pytest.mark.parametrize("h,w,D", [
+    (3, 16, 17), (2, 47, 32), (18, 33, 31),   # two disparities per lane, path lengths around the 16-step ring
+    (5, 31, 48), (4, 32, 50), (33, 20, 64),   # four; the last lane's word partly past D
+    (3, 90, 65), (2, 64, 128), (3, 70, 132),  # eight and sixteen
+])
+def test_path_lengths_and_lane_splits(h, w, D):
+    rng = np.random.default_rng(h * 100 + w + D)
+    cl = rng.integers(0, 2 ** 62, (2, h, w), dtype=np.uint64)
+    cr = np.roll(cl, -3, axis=2) ^ rng.integers(0, 2 ** 4, (2, h, w), dtype=np.uint64)
+    _check(cl, cr, D, 62, 10, 120)
+    _check(cl, cr, D, 62, 0, 192)             # path costs up to the uint8 limit
+
+
+@pytest.mark.parametrize("h,w,D,top", [
+    (2, 1, 4, 4), (3, 63, 16, 16), (2, 65, 16, 16), (4, 257, 48, 48), (2, 700, 256, 256),
+    (3, 100, 8, 40),                          # disparities past D: the row is searched
+    (1, 8192, 32, 32), (1, 8193, 32, 32),     # the widest row with the table, the first without
+])
+def test_single_matching_phase_rows(h, w, D, top):
+    import paper_2305_11566_amd as sv
+    rng = np.random.default_rng(w + D)
+    d = rng.integers(0, top, (2, h, w), dtype=np.uint8)
+    d[1] = np.minimum(np.arange(w)[None] // 5 % D, top - 1)
+    got = sv.sv_smp_median(cuda(d), D)
+    alias = cuda(d)
+    sv.sv_smp_median(alias, D, out=alias)
+    torch.cuda.synchronize()
+    ref = oracle.median3(oracle.smp(d, D))
+    assert (got.cpu().numpy() == ref).all()
+    assert (alias.cpu().numpy() == ref).all()

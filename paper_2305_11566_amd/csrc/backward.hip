@@ -295,7 +295,8 @@ static sv_status dgrad(const NetShape &ns, const void *packed, int li, ConvSrc d
     p.add = add; p.add_pitch = add_pitch; p.add_coff = add_coff;
     p.mask = mask; p.mask_pitch = mask_pitch;
     const int ks = ns.ly[li].k;
-    const int cfg = cout_needed <= 16 ? 5 : (cout_needed <= 32 ? 2 : 0);
+    const int cfg = ks == 3 ? conv_default_tile(ns.dtype, 1, dy.C, cout_needed, B, Hi, Wi)
+                            : (cout_needed <= 16 ? 5 : (cout_needed <= 32 ? 2 : 0));
     return launch_conv(ns.dtype, ks, 1, cfg, p, st);
 }
 
@@ -350,7 +351,7 @@ sv_status net_backward(const NetShape &ns, const void *packed, const void *saved
             p.wpk = (const char *)packed + ns.w_off[li];
             p.bias = (const float *)((const char *)packed + ns.b_off[li]);
             p.out = out; p.out_pitch = cout; p.act = 1;
-            return launch_conv(dt, 3, 2, net_default_cfg(ns, li, B * h[ko] * wd[ko]), p, st);
+            return launch_conv(dt, 3, 2, net_default_cfg(ns, li, lv, B), p, st);
         };
         SV_TRY(launch_enc1(dt, disp, img, (float)ns.f / 256.0f, B, h[0], wd[0], h[1], wd[1], c1,
                            (const char *)packed + ns.w_off[L_E1], ns.n_pad[L_E1], ns.cin_pad[L_E1],

@@ -362,10 +362,7 @@ sv_status sv_batch_plan_create(const sv_vae_desc *desc, int max_n, int max_H, in
     pl->dsplit = cost_wta_split_for(max_n, mx.h[0], mx.w[0], max_D);
     pl->cen_th = census_tile_height(max_n, mx.h[0], mx.w[0]);
     pl->fin_th = gather_tile_h(ns.f, (long long)max_n * max_H * max_W);
-    for (int i = 0; i < NLAYERS; ++i) {
-        const int lvl = i == L_E1 ? 1 : (i == L_E2 ? 2 : (i <= L_G3 ? 3 : (i == L_G2 ? 2 : (i == L_G1 ? 1 : 0))));
-        pl->cfg[i] = net_default_cfg(ns, i, mx.h[lvl] * mx.w[lvl]);
-    }
+    for (int i = 0; i < NLAYERS; ++i) pl->cfg[i] = net_default_cfg(ns, i, mx, max_n);
     int ds;
     int cfg[NLAYERS];
     if (tuned_lookup(ns, max_n, max_H, max_W, cfg, &ds)) {
@@ -544,7 +541,7 @@ sv_status sv_autotune(const sv_vae_desc *desc, int B, int H, int W, int D, int w
     // tuning changes no process-wide setting and other threads' calls are
     // unaffected
     int best_cfg[NLAYERS], cur[NLAYERS];
-    for (int i = 0; i < NLAYERS; ++i) best_cfg[i] = cur[i] = net_heuristic_cfg(ns, i);
+    for (int i = 0; i < NLAYERS; ++i) best_cfg[i] = cur[i] = net_heuristic_cfg(ns, i, net_levels(ns, H, W), B);
     if (r == SV_OK) {
         // census once, then every lane split of the cost + WTA kernel
         r = launch_reduce_census((uint8_t *)(d + o_l), (uint8_t *)(d + o_r), B, H, W, W, ns.f, win_w,

@@ -206,6 +206,46 @@ int conv_persistent_cfg(int cfg) {
     return cfg;
 }
 
+// The tile shape for a 3x3 layer without an entry in the autotune cache (the
+// tile does not change results, so this is a matter of speed alone).
+//
+// A taller or wider tile spends less on staging its halo, its pixel table and
+// the weights, until the chip is left with idle CUs.  The line is kEnough = 400
+// workgroups (1.5 a CU): in every measured pair of neighbouring shapes the
+// larger tile won with 480 workgroups and lost with 240 (BF16 G0 of the
+// 1242x375 network: batch 4 16-row 14.4 / 8-row 19.0 / 4-row 22.7 us, batch 2
+// 12.6 / 10.6 / 14.3; G1: batch 8 18.3 / 14.2 / 18.9).  Below it the smallest
+// tiles; 16-channel layers take 16 rows (in 32-channel tiles) in 16-bit types
+// (64 pairs of 256x128, G0: 49 against 59 us) but not in FP32 (81 against 66),
+// where half the products would be padding.  INT8 keeps to 32 channels, its
+// accumulators and staging registers allow two workgroups a CU there (G2 at
+// batch 64 101 against 118 us, E2 50 against 62).
+int conv_default_tile(int dtype, int stride, int cin, int cout, int B, int Ho, int Wo) {
+    enum { T4_64 = 0, T8_64 = 1, T4_32 = 2, T8_32 = 3, T2_64 = 4, T4_16 = 5, T4_16_K4 = 6, T4_32_K2 = 7, T4_16_K2 = 8,
+           T2_32_K2 = 11, T16_32 = 16 };
+    constexpr long long kEnough = 400;
+    auto wgs = [&](int th, int tn) { return (long long)B * cdiv(Ho, th) * cdiv(Wo, 16) * cdiv(cout, tn); };
+    const bool f32 = dtype == SV_F32, i8 = dtype == SV_I8;
+    if (stride == 1) {
+        if (cout <= 16) return !f32 && wgs(16, 32) >= kEnough ? T16_32 : T4_16;
+        if (cout <= 32) {
+            if (wgs(16, 32) >= kEnough) return T16_32;
+            if (wgs(8, 32) >= kEnough) return T8_32;
+            if (wgs(4, 32) >= kEnough) return T4_32;
+            return f32 || cin >= 96 ? T4_16_K2 : T4_16;
+        }
+        if (!i8 && wgs(8, 64) >= kEnough) return T8_64;
+        if (wgs(8, 32) >= kEnough) return T8_32;
+        if (wgs(4, 32) >= kEnough) return T4_32_K2;
+        return f32 ? T4_16_K4 : T2_32_K2;
+    }
+    if (cout <= 32) return wgs(4, 32) >= kEnough ? T4_32 : T4_16;
+    if (i8 && wgs(8, 32) >= kEnough) return T8_32;
+    if (wgs(2, 64) >= kEnough) return f32 && wgs(4, 32) >= 4 * kEnough ? T4_32 : T2_64;
+    if (cin >= 64 && wgs(2, 64) >= kEnough / 2) return T2_64;
+    return f32 || cin >= 64 ? T2_32_K2 : T4_16;
+}
+
 bool conv_cfg_projects(int cfg, int cout) {
     if (cfg < 0) return false;
     const CfgDesc &c = kCfgs[cfg % kNumTiles];

@@ -272,6 +272,8 @@ sv_status launch_final_gather_tab(const PairTable *tab, int grid, const float *T
 // whether a conv tile configuration can carry the projection epilogue for a
 // layer with cout output channels (one channel tile, all of it in each wave)
 bool conv_cfg_projects(int cfg, int cout);
+// the tile shape for a 3x3 layer of this size that nothing was tuned for
+int conv_default_tile(int dtype, int stride, int cin, int cout, int B, int Ho, int Wo);
 // the configuration a persistent pair-table launch runs for cfg
 int conv_persistent_cfg(int cfg);
 sv_status launch_final(int dtype, const void *G0, int c1, const uint8_t *disp, const uint8_t *img,

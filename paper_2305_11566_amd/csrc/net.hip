@@ -129,8 +129,13 @@ int net_get_cfg_override(int dtype, int layer) {
                                                                        : -1;
 }
 
-int net_heuristic_cfg(const NetShape &ns, int layer) {
+int net_heuristic_cfg(const NetShape &ns, int layer, const Levels &lv, int B) {
+    static const int out_level[NLAYERS] = {1, 2, 3, 3, 3, 2, 1, 0, 0};
     const int cout = layer == L_F ? 16 : ns.ly[layer].cout;
+    if (ns.ly[layer].k == 3 && layer != L_F) {
+        const int k = out_level[layer];
+        return conv_default_tile(ns.dtype, ns.ly[layer].stride, ns.ly[layer].cin, cout, B, lv.h[k], lv.w[k]);
+    }
     if (cout <= 16) return 5;   // th4_tn16
     if (cout <= 32) return 2;   // th4_tn32
     return 0;                   // th4_tn64
@@ -146,19 +151,19 @@ int net_g0_proj_cfg(const NetShape &ns, int cfg) {
     return c;
 }
 
-int net_default_cfg(const NetShape &ns, int layer, int M) {
+int net_default_cfg(const NetShape &ns, int layer, const Levels &lv, int B) {
     const int ov = net_get_cfg_override(ns.dtype, layer);
     if (ov >= 0 && ov < conv_num_cfgs()) return ov;
-    (void)M;
-    return net_heuristic_cfg(ns, layer);
+    return net_heuristic_cfg(ns, layer, lv, B);
 }
 
 void net_layer_cfgs(const NetShape &ns, int B, int H, int W, int *cfg) {
     int tuned[NLAYERS];
     const bool have = tuned_lookup(ns, B, H, W, tuned, nullptr);
+    const Levels lv = net_levels(ns, H, W);
     for (int i = 0; i < NLAYERS; ++i) {
         const int ov = net_get_cfg_override(ns.dtype, i);
-        cfg[i] = ov >= 0 ? ov : (have ? tuned[i] : net_default_cfg(ns, i, 0));
+        cfg[i] = ov >= 0 ? ov : (have ? tuned[i] : net_default_cfg(ns, i, lv, B));
         if (i < L_F) cfg[i] = conv_resolve_cfg(ns.dtype, ns.ly[i].k, ns.ly[i].stride, cfg[i]);
     }
 }

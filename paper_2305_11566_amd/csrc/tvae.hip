@@ -175,7 +175,10 @@ struct TvCfgInit {
 std::mutex g_tv_mu;
 std::map<std::tuple<int, int, int, int, int>, std::array<int, T_NL>> g_tv_tuned;
 
-// Default: tile th4_tn16 / th4_tn32 by output width; grids of fewer than 256
+// Default: tile th4_tn16 / th4_tn32 by output width (EN_2, whose 32 outputs
+// leave half the workgroups of the other coarse layers: th4_tn16 below 256
+// workgroups, 4.7 us of a 163 us pass at batch 1, th8_tn32 where that still
+// gives 200, 5 us at batch 16); grids of fewer than 256
 // workgroups (the coarse levels of small batches) split the reduction over
 // up to four channel ranges so that more CUs take part.
 int tv_heuristic_cfg(int layer, int B, int Ho, int Wo) {
@@ -184,6 +187,10 @@ int tv_heuristic_cfg(int layer, int B, int Ho, int Wo) {
     const long long nwg = (long long)cdiv(Wo, 16) * cdiv(Ho, 4) * B * cdiv(kLayers[layer].cout, tn);
     int split = 1;
     while (split < CONV_MAX_SPLIT && nwg * split < 256) ++split;
+    if (layer == T_EN2) {
+        if (nwg < 256) return 5 /* th4_tn16 */ + conv_num_tiles() * (split - 1);
+        if ((long long)cdiv(Wo, 16) * cdiv(Ho, 8) * B >= 200) return 3 /* th8_tn32 */;
+    }
     return tile + conv_num_tiles() * (split - 1);
 }
 

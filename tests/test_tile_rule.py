@@ -1,0 +1,32 @@
+"""The tile shapes of layers that nothing was tuned for: valid for every size
+and width, never a split of the reduction (the batch plan, which does not
+split, has to equal the single calls bit for bit), and taller for larger
+grids.  Host code only: no GPU."""
+import ctypes
+
+import pytest
+
+from paper_2305_11566_amd import _lib
+
+
+def _names(c, latent, f, dtype, B, H, W):
+    d = _lib.make_desc(*c, latent, f, dtype)
+    arr = (ctypes.c_int * 9)()
+    assert _lib.lib().sv_layer_cfgs(ctypes.byref(d), B, H, W, arr) == 0
+    return [_lib.lib().sv_conv_cfg_name(a).decode() for a in arr]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16", "i8"])
+@pytest.mark.parametrize("c,latent", [((8, 8, 8), 8), ((16, 32, 64), 64), ((32, 64, 128), 128), ((40, 96, 256), 256)])
+def test_every_size_has_an_unsplit_tile(monkeypatch, tmp_path, dtype, c, latent):
+    monkeypatch.setenv("SV_AUTOTUNE_CACHE", str(tmp_path / "none.tsv"))
+    for f, H, W in ((1, 1, 1), (2, 17, 33), (4, 375, 1242), (2, 256, 512), (8, 2000, 3000)):
+        for B in (1, 2, 7, 64, 500):
+            for n in _names(c, latent, f, dtype, B, H, W):
+                assert n.startswith("th") and "_s" not in n, (n, f, H, W, B)
+
+
+def test_larger_grids_take_taller_tiles(monkeypatch, tmp_path):
+    monkeypatch.setenv("SV_AUTOTUNE_CACHE", str(tmp_path / "none.tsv"))
+    rows = [int(_names((32, 64, 128), 128, 4, "bf16", B, 375, 1242)[7][2:].split("_")[0]) for B in (1, 2, 4, 64)]
+    assert rows == [4, 8, 16, 16]

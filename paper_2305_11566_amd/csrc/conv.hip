@@ -258,60 +258,7 @@ void conv_cfg_tile(int cfg, int &TH, int &TN) {
     TN = kCfgs[cfg % kNumTiles].TN;
 }
 
-// ---- weight packing ---------------------------------------------------------------
-// mode 0: forward [tap][n = out][c = in]; mode 1: the final layer, one row
-// per source tap; mode 2: adjoint [tap'][n = in][c = out] with the kernel
-// flipped (tap' = (k-1-u)*k + (k-1-v)), so the input gradient is an ordinary
-// convolution of the output gradient.
-template <int DT>
-__global__ void k_pack(const float *__restrict__ w, int Cout, int Cin, int k, int n_pad, int cin_pad,
-                       int mode, typename Elem<DT>::T *__restrict__ dst) {
-    const int tap_split = mode == 1;
-    const int taps = tap_split ? 1 : k * k;
-    const size_t total = (size_t)taps * n_pad * cin_pad;
-    for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < total;
-         e += (size_t)gridDim.x * blockDim.x) {
-        const int c = (int)(e % cin_pad);
-        const int n = (int)((e / cin_pad) % n_pad);
-        const int tap = (int)(e / ((size_t)cin_pad * n_pad));
-        float val = 0.f;
-        if (tap_split) {
-            // one output row per source tap of the single-output layer
-            if (n < k * k && c < Cin) val = w[(size_t)c * k * k + n];
-        } else if (mode == 2) {
-            // n runs over the layer's inputs, c over its outputs
-            if (n < Cin && c < Cout) val = w[((size_t)c * Cin + n) * k * k + (k * k - 1 - tap)];
-        } else if (n < Cout && c < Cin) {
-            val = w[((size_t)n * Cin + c) * k * k + tap];
-        }
-        dst[e] = Elem<DT>::make(val);
-    }
-}
-
-sv_status launch_pack(int dtype, const float *w, int Cout, int Cin, int k, int n_pad, int cin_pad,
-                      int tap_split, void *dst, hipStream_t s) {
-    const size_t total = (size_t)(tap_split == 1 ? 1 : k * k) * n_pad * cin_pad;
-    const int blocks = (int)((total + 255) / 256 < 1024 ? (total + 255) / 256 : 1024);
-    switch (dtype) {
-    case SV_F32:
-        hipLaunchKernelGGL(k_pack<SV_F32>, dim3(blocks), dim3(256), 0, s, w, Cout, Cin, k, n_pad,
-                           cin_pad, tap_split, (float *)dst);
-        break;
-    case SV_BF16:
-        hipLaunchKernelGGL(k_pack<SV_BF16>, dim3(blocks), dim3(256), 0, s, w, Cout, Cin, k, n_pad,
-                           cin_pad, tap_split, (uint16_t *)dst);
-        break;
-    case SV_F16:
-        hipLaunchKernelGGL(k_pack<SV_F16>, dim3(blocks), dim3(256), 0, s, w, Cout, Cin, k, n_pad,
-                           cin_pad, tap_split, (uint16_t *)dst);
-        break;
-    default:
-        return SV_ERR_DTYPE;
-    }
-    SV_LAUNCH_CHECK("k_pack");
-    return SV_OK;
-}
-
+// ---- INT8: weight packing and the activations' maxima -------------------------------
 // INT8 packing: one workgroup per output row n.  a = max |w[n]| over its
 // inputs and taps (FP32), code = clamp(rint(w * (127 / a)), -127, 127),
 // scale = a / 127; rows past Cout and columns past Cin are 0.

@@ -174,12 +174,35 @@ constexpr size_t CONV_PART_CAP = (size_t)16 << 20;
 int conv_num_cfgs();
 const char *conv_cfg_name(int cfg);
 
-// Packs canonical OIHW FP32 weights of one layer into [taps][n_pad][cin_pad].
-// mode 0: forward rows = output channels; mode 1 (final layer): taps = 1 and
-// row t = source tap t; mode 2: adjoint, rows = input channels, columns =
-// output channels, kernel flipped.
-sv_status launch_pack(int dtype, const float *w, int Cout, int Cin, int k, int n_pad, int cin_pad,
-                      int mode, void *dst, hipStream_t s);
+// Packing of canonical OIHW FP32 weights into the kernels' layout: a list of
+// pieces, each [taps][n_pad][cin_pad] in dtype dt, written by one launch.
+// PK_FWD: rows = outputs (aux 1: the kernel flipped); PK_ADJ: rows = inputs,
+// columns = outputs (aux 1: flipped); PK_TAPROWS: the taps of a layer with one
+// output as rows; PK_BIAS: cout values of n_pad; the others are pieces of the
+// Table I network (see pack_value).
+enum PackKind { PK_FWD = 0, PK_ADJ, PK_TAPROWS, PK_BIAS, PK_FE, PK_Y, PK_YADJ, PK_PHASE };
+struct PackTask {
+    const float *w;
+    void *dst;
+    int first;  // first workgroup (set by launch_pack)
+    uint16_t cout, cin, n_pad, cin_pad;
+    uint8_t kind, dt, k, aux;
+};
+__host__ __device__ inline int pack_total(const PackTask &t) {
+    if (t.kind == PK_BIAS) return t.n_pad;
+    const int taps = t.kind == PK_TAPROWS || t.kind == PK_Y || t.kind == PK_YADJ ? 1 : (t.kind == PK_PHASE ? 9 : t.k * t.k);
+    return taps * t.n_pad * t.cin_pad;
+}
+struct PackList {
+    static constexpr int MAX = 48;
+    int n;
+    PackTask task[MAX];
+    void add(int kind, int dt, const float *w, int cout, int cin, int k, int n_pad, int cin_pad, int aux, void *dst) {
+        task[n++] = PackTask{w, dst, 0, (uint16_t)cout, (uint16_t)cin, (uint16_t)n_pad, (uint16_t)cin_pad,
+                             (uint8_t)kind, (uint8_t)dt, (uint8_t)k, (uint8_t)aux};
+    }
+};
+sv_status launch_pack(PackList &list, hipStream_t s);
 // INT8 forward packing: codes [taps][n_pad][cin_pad] and the per-row scales
 // (FP32 [n_pad], 0 past Cout)
 sv_status launch_pack_i8(const float *w, int Cout, int Cin, int k, int n_pad, int cin_pad, int8_t *dst,

@@ -447,24 +447,23 @@ sv_status net_forward(const NetShape &ns, const void *packed, const uint8_t *dis
 }
 
 sv_status net_pack(const NetShape &ns, const float *params, void *packed, hipStream_t st) {
+    PackList list{};
+    char *P = (char *)packed;
     for (int i = 0; i < NLAYERS; ++i) {
         const LayerSpec &l = ns.ly[i];
         const float *w = params + ns.p_off[i];
-        if (ns.dtype == SV_I8 && i != L_F)
-            SV_TRY(launch_pack_i8(w, l.cout, l.cin, l.k, ns.n_pad[i], ns.cin_pad[i],
-                                  (int8_t *)((char *)packed + ns.w_off[i]),
-                                  (float *)((char *)packed + ns.s_off[i]), st));
+        if (i == L_F)
+            list.add(PK_TAPROWS, SV_F32, w, l.cout, l.cin, l.k, ns.n_pad[i], ns.cin_pad[i], 0, P + ns.w_off[i]);
+        else if (ns.dtype == SV_I8)
+            SV_TRY(launch_pack_i8(w, l.cout, l.cin, l.k, ns.n_pad[i], ns.cin_pad[i], (int8_t *)(P + ns.w_off[i]),
+                                  (float *)(P + ns.s_off[i]), st));
         else
-            SV_TRY(launch_pack(i == L_F ? SV_F32 : ns.dtype, w, l.cout, l.cin, l.k, ns.n_pad[i],
-                               ns.cin_pad[i], i == L_F ? 1 : 0, (char *)packed + ns.w_off[i], st));
+            list.add(PK_FWD, ns.dtype, w, l.cout, l.cin, l.k, ns.n_pad[i], ns.cin_pad[i], 0, P + ns.w_off[i]);
         if (ns.bw_off[i])
-            SV_TRY(launch_pack(ns.dtype, w, l.cout, l.cin, l.k, ns.bn_pad[i], ns.bcin_pad[i], 2,
-                               (char *)packed + ns.bw_off[i], st));
-        const float *b = w + (size_t)l.cout * l.cin * l.k * l.k;
-        SV_HIP(hipMemcpyAsync((char *)packed + ns.b_off[i], b, sizeof(float) * l.cout,
-                              hipMemcpyDeviceToDevice, st));
+            list.add(PK_ADJ, ns.dtype, w, l.cout, l.cin, l.k, ns.bn_pad[i], ns.bcin_pad[i], 1, P + ns.bw_off[i]);
+        list.add(PK_BIAS, SV_F32, w + (size_t)l.cout * l.cin * l.k * l.k, l.cout, 0, 1, l.cout, 1, 0, P + ns.b_off[i]);
     }
-    return SV_OK;
+    return launch_pack(list, st);
 }
 
 }  // namespace sv

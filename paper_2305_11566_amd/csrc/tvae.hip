@@ -213,211 +213,41 @@ void tv_layer_cfgs(int dtype, int f, int B, int H, int W, int *cfg) {
 }
 
 // ---- packing ------------------------------------------------------------------------
-// One job writes the rows [row0, row0 + cout) of a packed layer from one
-// canonical layer: column c of the packed row reads canonical input channel
-// cmap[c] (-1: zero); flip turns a deconvolution into the equivalent
-// correlation over the zero-inserted input; proj packs the upsampling layer as
-// one row per tap.
-struct PackJob {
-    const float *w;   // canonical weights of the layer
-    int cout, cin, k, row0, taps, n_pad, cin_pad, flip, proj;
-    int cmap[96];
-};
-
-template <int DT>
-__global__ void k_tv_pack_t(const PackJob j, typename Elem<DT>::T *__restrict__ dst) {
-    const int rows = j.proj ? TV_TAPS : j.cout;
-    const int total = j.taps * rows * j.cin_pad;
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
-        const int c = e % j.cin_pad;
-        const int r = (e / j.cin_pad) % rows;
-        const int tap = e / (j.cin_pad * rows);
-        const int ci = c < 96 ? j.cmap[c] : -1;
-        float v = 0.f;
-        if (ci >= 0) {
-            if (j.proj) v = j.w[(size_t)ci * j.k * j.k + r];  // output channel 0, tap r
-            else v = j.w[((size_t)r * j.cin + ci) * j.k * j.k + (j.flip ? j.k * j.k - 1 - tap : tap)];
-        }
-        dst[((size_t)tap * j.n_pad + j.row0 + r) * j.cin_pad + c] = Elem<DT>::make(v);
-    }
-}
-
-// Adjoint pack of one launched layer: dst[tap][n][c] with n over the layer's
-// inputs (canonical input channel rmap[n]) and c over its outputs.  A
-// convolution's input gradient correlates the output gradient with the
-// flipped kernel (over the zero-inserted gradient for stride 2); a
-// deconvolution's is the stride-2 correlation with the kernel as it is; proj:
-// the upsampling layer, one column per tap.
-struct AdjJob {
-    const float *w;
-    int cout, cin, k, rows, cols, taps, n_pad, cin_pad, flip, proj;
-    int rmap[96];
-};
-
-template <int DT>
-__global__ void k_tv_pack_adj(const AdjJob j, typename Elem<DT>::T *__restrict__ dst) {
-    const int total = j.taps * j.n_pad * j.cin_pad;
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
-        const int c = e % j.cin_pad;
-        const int n = (e / j.cin_pad) % j.n_pad;
-        const int tap = e / (j.cin_pad * j.n_pad);
-        float v = 0.f;
-        const int ci = n < j.rows ? j.rmap[n] : -1;
-        if (ci >= 0 && c < j.cols) {
-            if (j.proj) v = j.w[(size_t)ci * j.k * j.k + c];  // output channel 0, tap c
-            else v = j.w[((size_t)c * j.cin + ci) * j.k * j.k + (j.flip ? j.k * j.k - 1 - tap : tap)];
-        }
-        dst[e] = Elem<DT>::make(v);
-    }
-}
-
-// One parity class (py, px) of a stride-2, padding-2 5x5 deconvolution as a
-// 3x3, padding-1 correlation over the un-inserted input: output 2a + py takes
-// input row a - 1 + t with the weight row u = py + 4 - 2t (none outside 0..4),
-// and likewise for columns.
-template <int DT>
-__global__ void k_tv_pack_phase(const float *__restrict__ w, int cout, int cin, int n_pad, int cin_pad, int py,
-                                int px, typename Elem<DT>::T *__restrict__ dst) {
-    const int total = 9 * n_pad * cin_pad;
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
-        const int c = e % cin_pad;
-        const int o = (e / cin_pad) % n_pad;
-        const int tap = e / (cin_pad * n_pad);
-        const int u = py + 4 - 2 * (tap / 3), v = px + 4 - 2 * (tap % 3);
-        float val = 0.f;
-        if (o < cout && c < cin && u >= 0 && u < TV_K && v >= 0 && v < TV_K)
-            val = w[(((size_t)o * cin + c) * TV_K + u) * TV_K + v];
-        dst[e] = Elem<DT>::make(val);
-    }
-}
-
 __global__ void k_zero_bytes(uint32_t *__restrict__ p, size_t n_words) {
     for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < n_words; e += (size_t)gridDim.x * blockDim.x)
         p[e] = 0u;
 }
 
-__global__ void k_tv_bias(const float *__restrict__ b, int n, float *__restrict__ dst) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] = b[i];
-}
-
-sv_status run_pack_job(int dt, const PackJob &j, void *dst, hipStream_t st) {
-    const int rows = j.proj ? TV_TAPS : j.cout;
-    const int total = j.taps * rows * j.cin_pad;
-    const int blocks = std::min((total + 255) / 256, 1024);
-    switch (dt) {
-    case SV_F32: hipLaunchKernelGGL(k_tv_pack_t<SV_F32>, dim3(blocks), dim3(256), 0, st, j, (float *)dst); break;
-    case SV_BF16: hipLaunchKernelGGL(k_tv_pack_t<SV_BF16>, dim3(blocks), dim3(256), 0, st, j, (uint16_t *)dst); break;
-    case SV_F16: hipLaunchKernelGGL(k_tv_pack_t<SV_F16>, dim3(blocks), dim3(256), 0, st, j, (uint16_t *)dst); break;
-    default: return SV_ERR_DTYPE;
-    }
-    SV_LAUNCH_CHECK("k_tv_pack");
-    return SV_OK;
-}
-
+// A deconvolution's stride-1 form over the zero-inserted input is the
+// correlation with the flipped kernel; its polyphase packs keep the kernel.  A
+// convolution's input gradient correlates the output gradient with the flipped
+// kernel (over the zero-inserted gradient for stride 2); a deconvolution's is
+// the stride-2 correlation with the kernel as it is.
 sv_status tv_pack(const TvShape &s, const float *params, void *packed, hipStream_t st) {
-    // zero padding rows and columns first (a fill kernel, not a memset node)
-    const size_t words = s.bytes / 4;
-    hipLaunchKernelGGL(k_zero_bytes, dim3((unsigned)std::min<size_t>((words + 255) / 256, 4096)), dim3(256), 0, st,
-                       (uint32_t *)packed, words);
-    SV_LAUNCH_CHECK("k_zero_bytes");
+    static constexpr int kCanonOf[T_NL] = {C_FE1, C_EN1, C_EN1R, C_EN2, C_EN2R, C_MS, C_D1, C_D1R, C_D2, C_D2R, C_D, C_Y};
+    PackList list{};
     char *P = (char *)packed;
-    auto job = [&](int canon, int layer, int row0, bool flip, auto colmap) -> sv_status {
-        PackJob j{};
-        const CanonLayer &c = kCanon[canon];
-        j.w = params + canon_off(canon);
-        j.cout = c.cout; j.cin = c.cin; j.k = c.k; j.row0 = row0;
-        j.proj = layer == T_YP;
-        j.taps = j.proj ? 1 : c.k * c.k;
-        j.n_pad = s.n_pad[layer]; j.cin_pad = s.cin_pad[layer];
-        j.flip = flip;
-        for (int q = 0; q < 96; ++q) j.cmap[q] = q < j.cin_pad ? colmap(q) : -1;
-        SV_TRY_STATUS(run_pack_job(layer == T_YP ? SV_F32 : s.dtype, j, P + s.w_off[layer], st));
-        // bias of these rows (the projection has none: the gather adds Y's bias)
-        if (!j.proj) {
-            hipLaunchKernelGGL(k_tv_bias, dim3(1), dim3(64), 0, st, j.w + (size_t)c.cout * c.cin * c.k * c.k, c.cout,
-                               (float *)(P + s.b_off[layer]) + row0);
-            SV_LAUNCH_CHECK("k_tv_bias");
-        }
-        return SV_OK;
-    };
-    auto ident = [](int cin) { return [cin](int q) { return q < cin ? q : -1; }; };
-    // FE: rows 0..31 read channel 0 (X_0), rows 32..63 channel 1 (X_1)
-    SV_TRY_STATUS(job(C_FE1, T_FE, 0, false, [](int q) { return q == 0 ? 0 : -1; }));
-    SV_TRY_STATUS(job(C_FE2, T_FE, 32, false, [](int q) { return q == 1 ? 0 : -1; }));
-    SV_TRY_STATUS(job(C_EN1, T_EN1, 0, false, ident(64)));
-    SV_TRY_STATUS(job(C_EN1R, T_EN1R, 0, false, ident(16)));
-    SV_TRY_STATUS(job(C_EN2, T_EN2, 0, false, ident(24)));
-    SV_TRY_STATUS(job(C_EN2R, T_EN2R, 0, false, ident(32)));
-    SV_TRY_STATUS(job(C_MS, T_MS, 0, false, ident(48)));
-    SV_TRY_STATUS(job(C_D1, T_D1, 0, false, ident(1)));
-    SV_TRY_STATUS(job(C_D1R, T_D1R, 0, false, ident(80)));
-    SV_TRY_STATUS(job(C_D2, T_D2, 0, true, ident(96)));
-    SV_TRY_STATUS(job(C_D2R, T_D2R, 0, false, ident(40)));
-    SV_TRY_STATUS(job(C_D, T_D, 0, true, ident(48)));
-    // projection columns: the level-1 map [D | FE_1 | FE_2], then X_0, X_1;
-    // the table's order is D & X_0 & FE_1 & FE_2 (X_1 does not enter)
-    SV_TRY_STATUS(job(C_Y, T_YP, 0, false, [](int q) { return q < 16 ? q : (q < 80 ? q + 1 : (q == 80 ? 16 : -1)); }));
-    // Y's bias goes to the projection's bias slot, read by the gather
-    hipLaunchKernelGGL(k_tv_bias, dim3(1), dim3(64), 0, st, params + canon_off(C_Y) + 81 * 25, 1,
-                       (float *)(P + s.b_off[T_YP]));
-    SV_LAUNCH_CHECK("k_tv_bias");
-    // polyphase packs of the stride-2 deconvolutions
-    for (int li : {T_D2, T_D}) {
-        const int canon = li == T_D2 ? C_D2 : C_D;
-        const CanonLayer &c = kCanon[canon];
-        for (int ph = 0; ph < 4; ++ph) {
-            const int total = 9 * s.n_pad[li] * s.cin_pad[li];
-            const int blocks = std::min((total + 255) / 256, 1024);
-            void *dst = P + s.ph_off[li][ph];
-            const float *w = params + canon_off(canon);
-            switch (s.dtype) {
-            case SV_F32: hipLaunchKernelGGL(k_tv_pack_phase<SV_F32>, dim3(blocks), dim3(256), 0, st, w, c.cout, c.cin, s.n_pad[li], s.cin_pad[li], ph >> 1, ph & 1, (float *)dst); break;
-            case SV_BF16: hipLaunchKernelGGL(k_tv_pack_phase<SV_BF16>, dim3(blocks), dim3(256), 0, st, w, c.cout, c.cin, s.n_pad[li], s.cin_pad[li], ph >> 1, ph & 1, (uint16_t *)dst); break;
-            default: hipLaunchKernelGGL(k_tv_pack_phase<SV_F16>, dim3(blocks), dim3(256), 0, st, w, c.cout, c.cin, s.n_pad[li], s.cin_pad[li], ph >> 1, ph & 1, (uint16_t *)dst); break;
-            }
-            SV_LAUNCH_CHECK("k_tv_pack_phase");
-        }
+    for (int li = 0; li < T_NL; ++li) {
+        const CanonLayer &c = kCanon[kCanonOf[li]];
+        const float *w = params + canon_off(kCanonOf[li]);
+        const float *bias = w + (size_t)c.cout * c.cin * c.k * c.k;
+        const bool deconv = li == T_D2 || li == T_D, proj = li == T_YP;
+        const int dt = proj ? SV_F32 : s.dtype;
+        list.add(li == T_FE ? PK_FE : (proj ? PK_Y : PK_FWD), dt, w, c.cout, c.cin, c.k, s.n_pad[li], s.cin_pad[li],
+                 deconv, P + s.w_off[li]);
+        // the projection has no bias of its own: Y's, in its slot, is read by the gather
+        float *bd = (float *)(P + s.b_off[li]);
+        list.add(PK_BIAS, SV_F32, bias, c.cout, 0, 1, li == T_FE ? 32 : s.n_pad[li], 1, 0, bd);
+        if (li == T_FE)
+            list.add(PK_BIAS, SV_F32, params + canon_off(C_FE2) + 32 * TV_TAPS, 32, 0, 1, 32, 1, 0, bd + 32);
+        if (kAdjRows[li])
+            list.add(proj ? PK_YADJ : PK_ADJ, dt, w, c.cout, c.cin, c.k, s.bn_pad[li], s.bcin_pad[li],
+                     !deconv && c.k > 1, P + s.bw_off[li]);
+        if (deconv)
+            for (int ph = 0; ph < 4; ++ph)
+                list.add(PK_PHASE, dt, w, c.cout, c.cin, c.k, s.n_pad[li], s.cin_pad[li], ph, P + s.ph_off[li][ph]);
     }
-    // adjoint packs (the backward pass)
-    auto adj = [&](int canon, int layer, bool flip, auto rowmap) -> sv_status {
-        AdjJob j{};
-        const CanonLayer &c = kCanon[canon];
-        j.w = params + canon_off(canon);
-        j.cout = c.cout; j.cin = c.cin; j.k = c.k;
-        j.proj = layer == T_YP;
-        j.rows = kAdjRows[layer];
-        j.cols = kLayers[layer].cout;
-        j.taps = kLayers[layer].k * kLayers[layer].k;
-        j.n_pad = s.bn_pad[layer]; j.cin_pad = s.bcin_pad[layer];
-        j.flip = flip;
-        for (int q = 0; q < 96; ++q) j.rmap[q] = q < j.rows ? rowmap(q) : -1;
-        const int total = j.taps * j.n_pad * j.cin_pad;
-        const int blocks = std::min((total + 255) / 256, 1024);
-        void *dst = P + s.bw_off[layer];
-        switch (layer == T_YP ? SV_F32 : s.dtype) {
-        case SV_F32: hipLaunchKernelGGL(k_tv_pack_adj<SV_F32>, dim3(blocks), dim3(256), 0, st, j, (float *)dst); break;
-        case SV_BF16: hipLaunchKernelGGL(k_tv_pack_adj<SV_BF16>, dim3(blocks), dim3(256), 0, st, j, (uint16_t *)dst); break;
-        default: hipLaunchKernelGGL(k_tv_pack_adj<SV_F16>, dim3(blocks), dim3(256), 0, st, j, (uint16_t *)dst); break;
-        }
-        SV_LAUNCH_CHECK("k_tv_pack_adj");
-        return SV_OK;
-    };
-    auto idr = [](int q) { return q; };
-    SV_TRY_STATUS(adj(C_EN1, T_EN1, true, idr));
-    SV_TRY_STATUS(adj(C_EN1R, T_EN1R, true, idr));
-    SV_TRY_STATUS(adj(C_EN2, T_EN2, true, idr));
-    SV_TRY_STATUS(adj(C_EN2R, T_EN2R, true, idr));
-    SV_TRY_STATUS(adj(C_MS, T_MS, false, idr));
-    SV_TRY_STATUS(adj(C_D1, T_D1, false, idr));
-    SV_TRY_STATUS(adj(C_D1R, T_D1R, true, idr));
-    SV_TRY_STATUS(adj(C_D2, T_D2, false, idr));
-    SV_TRY_STATUS(adj(C_D2R, T_D2R, true, idr));
-    SV_TRY_STATUS(adj(C_D, T_D, false, idr));
-    // the upsampling layer's rows: the level-1 channels [D | FE_1 | FE_2] in the
-    // table's order D & X_0 & FE_1 & FE_2 (X_0 needs no gradient)
-    SV_TRY_STATUS(adj(C_Y, T_YP, false, [](int q) { return q < 16 ? q : q + 1; }));
-    return SV_OK;
+    return launch_pack(list, st);
 }
 
 // ---- Eq. (8) and the final gather ------------------------------------------------

@@ -29,11 +29,14 @@ namespace sv {
 // would be zeros (E1: 2 column blocks instead of 9; FE: 4 instead of 25).  It
 // runs the FP32 instruction on the values rounded to the compute dtype.
 //
-// Measured on a training pass (the former kernel unfolded each tile tap by tap
-// in LDS, gave every wave its own blocks, and ran the deconvolutions over the
-// zero-inserted input): all layers of the BF16 network on 16 512x256 crops 610
-// -> 330 us, of the FP32 Table I network on four 1373 -> 310 us.  Staging
-// latency bounds the large 16-bit layers, the FP32 matrix rate the 5x5 ones.
+// Measured on a training pass: all layers of the BF16 network on 16 512x256
+// crops 200 us, of the FP32 Table I network on four 255 us (610 and 1373 us with
+// a kernel that unfolded each tile tap by tap in LDS, gave every wave its own
+// blocks, and ran the deconvolutions over the zero-inserted input).  Staging
+// bounds the large 16-bit layers: a tile's loads are issued together, one kind
+// of source at a time (per element, with the kinds' branches between them,
+// they cost a memory latency each: G0 132 us instead of 71).  The FP32 matrix
+// rate bounds the 5x5 ones.
 // ---------------------------------------------------------------------------
 struct WgradParams {
     ConvSrc src[2];
@@ -65,22 +68,30 @@ __device__ __forceinline__ u16x8 tr_frag(const uint16_t *p0, const uint16_t *p1)
     return r;
 }
 
-// N consecutive values of a map stored in sdt, as FP32
-template <int N>
-__device__ __forceinline__ void ld_vals(const void *base, size_t off, int sdt, float (&v)[N]) {
+// N consecutive values of U places of a map stored in sdt, as FP32: every load
+// is issued before the first conversion (a branch or conversion between them
+// would wait for each in turn)
+template <int N, int U>
+__device__ __forceinline__ void ld_vals(const void *base, const size_t (&off)[U], int sdt, float (&v)[U][N]) {
     if (sdt == SV_F32) {
+        f32x4 q[U][N / 4];
 #pragma unroll
-        for (int i = 0; i < N; i += 4) {
-            const f32x4 q = *(const f32x4 *)((const float *)base + off + i);
-            v[i] = q[0]; v[i + 1] = q[1]; v[i + 2] = q[2]; v[i + 3] = q[3];
-        }
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+            for (int i = 0; i < N / 4; ++i) q[k][i] = *(const f32x4 *)((const float *)base + off[k] + 4 * i);
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+            for (int i = 0; i < N; ++i) v[k][i] = q[k][i / 4][i % 4];
     } else {
+        typedef uint16_t hvec __attribute__((ext_vector_type(N)));
+        hvec q[U];
 #pragma unroll
-        for (int i = 0; i < N; i += 4) {
-            const u16x4 q = *(const u16x4 *)((const uint16_t *)base + off + i);
+        for (int k = 0; k < U; ++k) q[k] = *(const hvec *)((const uint16_t *)base + off[k]);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) v[i + k] = sdt == SV_BF16 ? bf16_bits_to_f32(q[k]) : f16_bits_to_f32(q[k]);
-        }
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+            for (int i = 0; i < N; ++i) v[k][i] = sdt == SV_BF16 ? bf16_bits_to_f32(q[k][i]) : f16_bits_to_f32(q[k][i]);
     }
 }
 
@@ -141,17 +152,21 @@ __global__ void __launch_bounds__(256, 2) k_wgrad(const WgradParams p)
         {
             const int og = tid % OG, o = o0 + og * 4;
             float v[ND][4];
+            size_t off[ND];
+            bool ok[ND];
 #pragma unroll
             for (int k = 0; k < ND; ++k) {
                 const int m = tid / OG + k * (256 / OG);
                 const int oy = oy0 + m / W::TW, ox = ox0 + m % W::TW;
-                const bool ok = m < W::MT && oy < p.Ho && ox < p.Wo && o < p.Cout;
-                const size_t off = ok ? (((size_t)b * p.Ho + oy) * p.Wo + ox) * p.dy_pitch + o : 0;
-                ld_vals<4>(p.dy, off, p.dy_sdt, v[k]);
+                ok[k] = m < W::MT && oy < p.Ho && ox < p.Wo && o < p.Cout;
+                off[k] = ok[k] ? (((size_t)b * p.Ho + oy) * p.Wo + ox) * p.dy_pitch + o : 0;
+            }
+            ld_vals<4, ND>(p.dy, off, p.dy_sdt, v);
+#pragma unroll
+            for (int k = 0; k < ND; ++k)
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    if (!ok || o + i >= p.Cout) v[k][i] = 0.f;
-            }
+                    if (!ok[k] || o + i >= p.Cout) v[k][i] = 0.f;
 #pragma unroll
             for (int k = 0; k < ND; ++k) {
                 const int m = tid / OG + k * (256 / OG);
@@ -210,56 +225,107 @@ __global__ void __launch_bounds__(256, 2) k_wgrad(const WgradParams p)
                     *(u16x8 *)&xpl[pix * W::CP + cg * GS] = q;
                 }
             };
-            constexpr int U = 4;  // elements whose loads are in flight together
+            // element k of this thread: its patch pixel, and whether that is in the input grid
+            auto place = [&](int k, int &pix, int &py, int &px) {
+                pix = tid / KCG + k * PSTEP;
+                py = pix / W::PW;
+                px = pix - py * W::PW;
+                const int yi = iy0 + py, xi = ix0 + px;
+                return pix < W::NPIX && yi >= 0 && yi < p.Hi && xi >= 0 && xi < p.Wi;
+            };
+            if (kind == SRC_TENSOR) {
+                // elements whose loads are in flight together; 36 accumulators leave registers for half
+                constexpr int U = OB * W::NB > 25 ? (NE < 3 ? NE : 3) : (NE < 6 ? NE : 6);
 #pragma unroll 1
-            for (int k0 = 0; k0 < NE; k0 += U) {
-                float v[U][GS];
+                for (int k0 = 0; k0 < NE; k0 += U) {
+                    float v[U][GS];
+                    size_t off[U];
+                    int pix[U];
+                    bool ok[U], own[U];
 #pragma unroll
-                for (int k = 0; k < U; ++k) {
-                    const int pix = tid / KCG + (k0 + k) * PSTEP;
-                    const int py = pix / W::PW, px = pix - py * W::PW;
-                    const int yi = iy0 + py, xi = ix0 + px;
-                    const bool ok = pix < W::NPIX && yi >= 0 && yi < p.Hi && xi >= 0 && xi < p.Wi;
+                    for (int k = 0; k < U; ++k) {
+                        int py, px;
+                        ok[k] = place(k0 + k, pix[k], py, px);
+                        own[k] = ok[k] && py >= W::PAD && py < W::PAD + W::TH * S && px >= W::PAD &&
+                                 px < W::PAD + W::TW * S;
+                        off[k] = ok[k] ? (((size_t)b * s.hs + iy0 + py) * s.ws + ix0 + px) * s.pitch + cb : cb;
+                    }
+                    ld_vals<GS, U>(s.ptr, off, sdt, v);
 #pragma unroll
-                    for (int i = 0; i < GS; ++i) v[k][i] = 0.f;
-                    if (kind == SRC_TENSOR) {
-                        const size_t off = ok ? (((size_t)b * s.hs + yi) * s.ws + xi) * s.pitch + cb : cb;
-                        ld_vals<GS>(s.ptr, off, sdt, v[k]);
+                    for (int k = 0; k < U; ++k) {
 #pragma unroll
                         for (int i = 0; i < GS; ++i)
-                            if (!ok) v[k][i] = 0.f;
-                        if (p.bias_src && ok && py >= W::PAD && py < W::PAD + W::TH * S && px >= W::PAD &&
-                            px < W::PAD + W::TW * S) {
+                            if (!ok[k]) v[k][i] = 0.f;
+                        if (p.bias_src && own[k]) {
 #pragma unroll
                             for (int i = 0; i < GS; ++i) sb[i] += v[k][i];
                         }
-                    } else if (kind == SRC_RESIZE) {
-                        int y0, y1, x0, x1;
-                        float ly, lx;
-                        bilin(ok ? yi : 0, s.hs, p.Hi, y0, y1, ly);
-                        bilin(ok ? xi : 0, s.ws, p.Wi, x0, x1, lx);
-                        const size_t rb = (size_t)b * s.hs;
-                        float a00[GS], a01[GS], a10[GS], a11[GS];
-                        ld_vals<GS>(s.ptr, ((rb + y0) * s.ws + x0) * s.pitch + cb, sdt, a00);
-                        ld_vals<GS>(s.ptr, ((rb + y0) * s.ws + x1) * s.pitch + cb, sdt, a01);
-                        ld_vals<GS>(s.ptr, ((rb + y1) * s.ws + x0) * s.pitch + cb, sdt, a10);
-                        ld_vals<GS>(s.ptr, ((rb + y1) * s.ws + x1) * s.pitch + cb, sdt, a11);
-#pragma unroll
-                        for (int i = 0; i < GS; ++i) {
-                            const float top = (1.f - lx) * a00[i] + lx * a01[i];
-                            const float bot = (1.f - lx) * a10[i] + lx * a11[i];
-                            v[k][i] = ok ? (1.f - ly) * top + ly * bot : 0.f;
-                        }
-                    } else if (kind == SRC_X0) {
-                        const size_t o = ok ? ((size_t)b * s.hs + yi) * s.ws + xi : 0;
-                        v[k][0] = ok ? s.scale0 * (float)((const uint8_t *)s.ptr)[o] : 0.f;
-                        v[k][1] = ok ? (float)s.img[o] * (1.0f / 256.0f) : 0.f;
+                        if (pix[k] < W::NPIX) put(pix[k], v[k]);
                     }
                 }
+            } else if (kind == SRC_RESIZE) {
+                constexpr int U = OB * W::NB > 25 || NE < 2 ? 1 : 2;
+#pragma unroll 1
+                for (int k0 = 0; k0 < NE; k0 += U) {
+                    float v[4 * U][GS];
+                    size_t off[4 * U];
+                    int pix[U];
+                    bool ok[U];
+                    float ly[U], lx[U];
+                    const size_t rb = (size_t)b * s.hs;
 #pragma unroll
-                for (int k = 0; k < U; ++k) {
-                    const int pix = tid / KCG + (k0 + k) * PSTEP;
-                    if (pix < W::NPIX) put(pix, v[k]);
+                    for (int k = 0; k < U; ++k) {
+                        int py, px, y0, y1, x0, x1;
+                        ok[k] = place(k0 + k, pix[k], py, px);
+                        bilin(ok[k] ? iy0 + py : 0, s.hs, p.Hi, y0, y1, ly[k]);
+                        bilin(ok[k] ? ix0 + px : 0, s.ws, p.Wi, x0, x1, lx[k]);
+                        off[4 * k] = ((rb + y0) * s.ws + x0) * s.pitch + cb;
+                        off[4 * k + 1] = ((rb + y0) * s.ws + x1) * s.pitch + cb;
+                        off[4 * k + 2] = ((rb + y1) * s.ws + x0) * s.pitch + cb;
+                        off[4 * k + 3] = ((rb + y1) * s.ws + x1) * s.pitch + cb;
+                    }
+                    ld_vals<GS, 4 * U>(s.ptr, off, sdt, v);
+#pragma unroll
+                    for (int k = 0; k < U; ++k) {
+                        float r[GS];
+#pragma unroll
+                        for (int i = 0; i < GS; ++i) {
+                            const float top = (1.f - lx[k]) * v[4 * k][i] + lx[k] * v[4 * k + 1][i];
+                            const float bot = (1.f - lx[k]) * v[4 * k + 2][i] + lx[k] * v[4 * k + 3][i];
+                            r[i] = ok[k] ? (1.f - ly[k]) * top + ly[k] * bot : 0.f;
+                        }
+                        if (pix[k] < W::NPIX) put(pix[k], r);
+                    }
+                }
+            } else {
+                constexpr int U = OB * W::NB > 25 ? 4 : 8;
+#pragma unroll 1
+                for (int k0 = 0; k0 < NE; k0 += U) {
+                    uint32_t dv[U], iv[U];
+                    int pix[U];
+                    bool ok[U];
+#pragma unroll
+                    for (int k = 0; k < U; ++k) {
+                        int py, px;
+                        ok[k] = place(k0 + k, pix[k], py, px) && kind == SRC_X0;
+                        const size_t o = ok[k] ? ((size_t)b * s.hs + iy0 + py) * s.ws + ix0 + px : 0;
+                        dv[k] = iv[k] = 0;
+                        if (kind == SRC_X0) {
+                            dv[k] = ((const uint8_t *)s.ptr)[o];
+                            iv[k] = s.img[o];
+                        }
+                    }
+#pragma unroll
+                    for (int k = 0; k < U; ++k) {
+                        float v[GS];
+#pragma unroll
+                        for (int i = 0; i < GS; ++i) v[i] = 0.f;
+                        if (ok[k]) {
+                            v[0] = s.scale0 * (float)dv[k];
+                            v[1] = (float)iv[k] * (1.0f / 256.0f);
+                        }
+                        if (pix[k] < W::NPIX) put(pix[k], v);
+                    }
                 }
             }
         }

@@ -25,47 +25,91 @@
 
 namespace sv {
 
+// The fine indices a coarse index i collects from along one axis (n_c coarse,
+// n_f fine samples): the first one, and for k < N the weight with which fine
+// index first + k reads i (0 where it does not).  Fine index Y reads i when its
+// source position (Y + 1/2) n_c / n_f - 1/2 lies within one of i; positions are
+// at least 1 / f apart for n_c = ceil(n_f / f), so N = 2 f + 1 covers the open
+// interval of length 2 from the index at or before its start.
+template <int N>
+__device__ __forceinline__ int adj_axis(int i, int n_c, int n_f, float (&w)[N]) {
+    const int num = (2 * i - 1) * n_f - n_c;
+    const int first = num <= 0 ? 0 : num / (2 * n_c);
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        int i0, i1;
+        float lam;
+        bilin(min(first + k, n_f - 1), n_c, n_f, i0, i1, lam);
+        const float v = (i0 == i ? 1.f - lam : 0.f) + (i1 == i ? lam : 0.f);
+        w[k] = first + k < n_f ? v : 0.f;
+    }
+    return first;
+}
+
 // ---------------------------------------------------------------------------
 // Bilinear resize adjoint (gather form) times the leaky-ReLU derivative of the
 // coarse map:  out[b][i][j][c] = lrelu'(mask[b][i][j][c]) *
-//   sum over fine (Y, X) of wy(Y -> i) wx(X -> j) in[b][Y][X][coff + c].
+//   sum over fine (Y, X) of wy(Y -> i) wx(X -> j) in[b][Y][X][coff + c],
+// for the halvings of the network (Hc = ceil(Hf / 2), Wc likewise).
+// A workgroup takes one coarse row and TJ columns, TJ C / 4 = 256 where it can;
+// the axis weights (an integer division each) are formed once per row and
+// column, a thread then reads its 5 x 5 fine positions of four channels, the
+// ones without weight as zeros.  Bound by reading the fine map (from L1 and L2
+// after the first time).
+// (BF16 network, 16 512x256 crops, three levels: 33 us; 77 us with the
+// weights recomputed by every thread for every fine pixel of a 9 x 9 window.)
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ float bilin_weight_to(int o, int n_in, int n_out, int i) {
-    int i0, i1;
-    float lam;
-    bilin(o, n_in, n_out, i0, i1, lam);
-    return (i0 == i ? 1.f - lam : 0.f) + (i1 == i ? lam : 0.f);
-}
+constexpr int RA_N = 5, RA_TJ = 64;
 
 template <int DT>
-__global__ void k_resize_adj(const float *__restrict__ in, int ipitch, int icoff, int Hf, int Wf,
-                             int Hc, int Wc, int C, const void *__restrict__ mask,
-                             float *__restrict__ out, int B)
+__global__ void __launch_bounds__(256)
+k_resize_adj(const float *__restrict__ in, int ipitch, int icoff, int Hf, int Wf,
+             int Hc, int Wc, int C, int TJ, const void *__restrict__ mask,
+             float *__restrict__ out)
 {
-    const int cg4 = C / 4;
-    const size_t n = (size_t)B * Hc * Wc * cg4;
-    for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < n;
-         e += (size_t)gridDim.x * blockDim.x) {
-        const int cg = (int)(e % cg4);
-        const size_t pix = e / cg4;
-        const int j = (int)(pix % Wc), i = (int)((pix / Wc) % Hc), b = (int)(pix / ((size_t)Wc * Hc));
-        const int ylo = max(0, ((i - 1) * Hf) / Hc - 1), yhi = min(Hf - 1, ((i + 2) * Hf) / Hc + 1);
-        const int xlo = max(0, ((j - 1) * Wf) / Wc - 1), xhi = min(Wf - 1, ((j + 2) * Wf) / Wc + 1);
+    __shared__ int xs[RA_TJ];
+    __shared__ float wx[RA_TJ][RA_N], wy[RA_N];
+    __shared__ int ysh;
+    const int i = blockIdx.y, b = blockIdx.z, j0 = blockIdx.x * TJ;
+    for (int t = threadIdx.x; t <= TJ; t += 256) {
+        float w[RA_N];
+        if (t < TJ) {
+            xs[t] = adj_axis<RA_N>(min(j0 + t, Wc - 1), Wc, Wf, w);
+#pragma unroll
+            for (int k = 0; k < RA_N; ++k) wx[t][k] = w[k];
+        } else {
+            ysh = adj_axis<RA_N>(i, Hc, Hf, w);
+#pragma unroll
+            for (int k = 0; k < RA_N; ++k) wy[k] = w[k];
+        }
+    }
+    __syncthreads();
+    const int cg4 = C / 4, Y0 = ysh;
+    for (int e = threadIdx.x; e < TJ * cg4; e += 256) {
+        const int jl = e / cg4, cg = e - jl * cg4, j = j0 + jl;
+        if (j >= Wc) break;
+        const int X0 = xs[jl];
+        const size_t pix = ((size_t)b * Hc + i) * Wc + j;
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        for (int Y = ylo; Y <= yhi; ++Y) {
-            const float wy = bilin_weight_to(Y, Hc, Hf, i);
-            if (wy == 0.f) continue;
-            for (int X = xlo; X <= xhi; ++X) {
-                const float wx = bilin_weight_to(X, Wc, Wf, j);
-                if (wx == 0.f) continue;
-                const float wgt = wy * wx;
-                const f32x4 v = *(const f32x4 *)(in + (((size_t)b * Hf + Y) * Wf + X) * ipitch + icoff + 4 * cg);
-                acc += wgt * v;
+#pragma unroll
+        for (int ky = 0; ky < RA_N; ++ky) {
+            const float wyk = wy[ky];
+            if (wyk == 0.f) continue;  // the whole workgroup's
+            const float *row = in + (((size_t)b * Hf + Y0 + ky) * Wf) * ipitch + icoff + 4 * cg;
+            f32x4 v[RA_N];
+#pragma unroll
+            for (int kx = 0; kx < RA_N; ++kx) v[kx] = *(const f32x4 *)(row + (size_t)min(X0 + kx, Wf - 1) * ipitch);
+#pragma unroll
+            for (int kx = 0; kx < RA_N; ++kx) {
+                const float wgt = wyk * wx[jl][kx];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[q] += wgt * (wgt != 0.f ? v[kx][q] : 0.f);
             }
         }
         const typename Elem<DT>::T *mk = (const typename Elem<DT>::T *)mask + pix * C + 4 * cg;
         f32x4 r;
-        for (int k = 0; k < 4; ++k) r[k] = acc[k] * (Elem<DT>::load(mk + k) > 0.f ? 1.f : 0.1f);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) r[q] = acc[q] * (Elem<DT>::load(mk + q) > 0.f ? 1.f : 0.1f);
         *(f32x4 *)(out + pix * C + 4 * cg) = r;
     }
 }
@@ -73,13 +117,14 @@ __global__ void k_resize_adj(const float *__restrict__ in, int ipitch, int icoff
 static sv_status launch_resize_adj(int dtype, const float *in, int ipitch, int icoff, int Hf, int Wf,
                                    int Hc, int Wc, int C, const void *mask, float *out, int B,
                                    hipStream_t st) {
-    const size_t n = (size_t)B * Hc * Wc * (C / 4);
-    const int blocks = (int)((n + 255) / 256 < 8192 ? (n + 255) / 256 : 8192);
+    const int tj = std::max(4, std::min(RA_TJ, 1024 / C));
+    const dim3 grid(cdiv(Wc, tj), Hc, B);
+    if (Hc > 65535 || B > 65535) return SV_ERR_SHAPE;
     switch (dtype) {
-#define SV_RA(D)                                                                              \
-    case D:                                                                                   \
-        hipLaunchKernelGGL(k_resize_adj<D>, dim3(blocks), dim3(256), 0, st, in, ipitch, icoff, \
-                           Hf, Wf, Hc, Wc, C, mask, out, B);                                 \
+#define SV_RA(D)                                                                                  \
+    case D:                                                                                       \
+        hipLaunchKernelGGL(k_resize_adj<D>, grid, dim3(256), 0, st, in, ipitch, icoff, Hf, Wf, Hc, \
+                           Wc, C, tj, mask, out);                                                 \
         break;
         SV_RA(SV_F32)
         SV_RA(SV_BF16)
@@ -97,56 +142,163 @@ static sv_status launch_resize_adj(int dtype, const float *in, int ipitch, int i
 //   dT_t(i) = sum over full-res q inside of A(q, i) * dY(q - (u-1, v-1))
 // (zero where q - delta leaves the image), then
 //   dpre0[c](i) = lrelu'(G0[c](i)) * sum_t W_F[c][t] dT_t(i)   for c < c1.
-// dT is written with 16 channels (9 used, the rest 0) for the weight gradient.
+// dT is written with FB_DT channels (9 used, the rest 0) for the weight gradient.
+//
+// A workgroup owns TI x 32 coarse pixels.  A is separable, so it stages the
+// tile's region of dout in LDS, sums along the rows for the three column shifts
+// (each fine row once, not once per coarse row and tap), then along the columns
+// for the three row shifts.  Its share of dout (the tiles' shares
+// partition the image) also goes into the bias gradient's sum.
+// Bound by its 116 B written a coarse pixel at c1 = 16.
+// (16 512x256 crops, f = 2: 30 us; 109 us with 9 taps of every fine pixel and
+// its weights per coarse pixel, and 10 us for a pass of its own for the sum.)
 // ---------------------------------------------------------------------------
-template <int DT>
-__global__ void k_final_bwd(const float *__restrict__ dout, int H, int W, int h, int w, int B,
-                            const void *__restrict__ wF, int wf_pitch, int c1,
-                            const void *__restrict__ G0, float *__restrict__ dT,
-                            float *__restrict__ dpre0)
+constexpr int FB_TJ = 32, FB_DT = 12;
+static inline int fb_ti(int f) { return f <= 2 ? 8 : (f <= 4 ? 4 : 2); }
+// rows (columns) of dout a tile of n coarse ones needs: the supports of the
+// first and last, shifted by up to one
+static inline int fb_span(int n, int f) { return (n + 1) * f + 2 * f + 4; }
+
+template <int DT, int F>
+__global__ void __launch_bounds__(256)
+k_final_bwd(const float *__restrict__ dout, int H, int W, int h, int w, int TI, int srows, int scols,
+            const float *__restrict__ wF, int wf_pitch, int c1,
+            const typename Elem<DT>::T *__restrict__ G0, float *__restrict__ dT,
+            float *__restrict__ dpre0, float *__restrict__ sum_part)
 {
-    const size_t n = (size_t)B * h * w;
-    for (size_t pix = blockIdx.x * (size_t)blockDim.x + threadIdx.x; pix < n;
-         pix += (size_t)gridDim.x * blockDim.x) {
-        const int j = (int)(pix % w), i = (int)((pix / w) % h), b = (int)(pix / ((size_t)w * h));
-        const int ylo = max(0, ((i - 1) * H) / h - 1), yhi = min(H - 1, ((i + 2) * H) / h + 1);
-        const int xlo = max(0, ((j - 1) * W) / w - 1), xhi = min(W - 1, ((j + 2) * W) / w + 1);
+    constexpr int N = 2 * F + 1;  // F >= f
+    extern __shared__ __attribute__((aligned(16))) float fsm[];
+    float *reg = fsm;                              // [srows][scols] of dout
+    float *hv = reg + srows * scols;               // [srows][3][FB_TJ]
+    float *wxs = hv + srows * 3 * FB_TJ;           // [FB_TJ][N]
+    float *wys = wxs + FB_TJ * N;                  // [TI][N]
+    int *xs = (int *)(wys + 8 * N);                // [FB_TJ], [8]
+    int *ys = xs + FB_TJ;
+    float *red = (float *)(ys + 8);                // [4]
+    const int tid = threadIdx.x, b = blockIdx.z;
+    const int i0 = blockIdx.y * TI, j0 = blockIdx.x * FB_TJ;
+    const int ni = min(TI, h - i0), nj = min(FB_TJ, w - j0);
+    if (tid < ni + nj) {
+        float wt[N];
+        const bool row = tid < ni;
+        const int k = row ? tid : tid - ni;
+        const int s = adj_axis<N>(row ? i0 + k : j0 + k, row ? h : w, row ? H : W, wt);
+        if (row) ys[k] = s;
+        else xs[k] = s;
+#pragma unroll
+        for (int q = 0; q < N; ++q) (row ? wys : wxs)[k * N + q] = wt[q];
+    }
+    __syncthreads();
+    // region of dout: one row / column before the first support to one after the last
+    const int R0 = ys[0] - 1, C0 = xs[0] - 1;
+    const int nr = min(srows, ys[ni - 1] + N + 1 - R0), nc = min(scols, xs[nj - 1] + N + 1 - C0);
+    const float *db = dout + (size_t)b * H * W;
+    // its share of the image, which its region covers: from i0 H / h to (i0 + ni) H / h
+    const int oy0 = i0 * H / h, oy1 = (i0 + ni) * H / h, ox0 = j0 * W / w, ox1 = (j0 + nj) * W / w;
+    float own = 0.f;
+    for (int e = tid; e < nr * nc; e += 256) {
+        const int r = e / nc, c = e - r * nc;
+        const int y = R0 + r, x = C0 + c;
+        const bool in = y >= 0 && y < H && x >= 0 && x < W;
+        const float v = in ? db[(size_t)y * W + x] : 0.f;
+        reg[r * scols + c] = v;
+        if (in && y >= oy0 && y < oy1 && x >= ox0 && x < ox1) own += v;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) own += __shfl_xor(own, o);
+    if ((tid & 63) == 0) red[tid >> 6] = own;
+    __syncthreads();
+    if (tid == 0)
+        sum_part[((size_t)b * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+    // along the rows: hv[r][v][j] = sum_k wx[j][k] dout[r][xs[j] + k - (v - 1)]
+    for (int e = tid; e < nr * FB_TJ; e += 256) {
+        const int r = e / FB_TJ, j = e % FB_TJ;
+        if (j >= nj) continue;
+        const float *row = reg + r * scols + xs[j] - C0 - 1;
+        float d[N + 2];
+#pragma unroll
+        for (int k = 0; k < N + 2; ++k) d[k] = row[min(k, nc - 1 - (xs[j] - C0 - 1))];
+        float a[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const float wk = wxs[j * N + k];
+#pragma unroll
+            for (int v = 0; v < 3; ++v) a[v] += wk != 0.f ? wk * d[k + 2 - v] : 0.f;
+        }
+#pragma unroll
+        for (int v = 0; v < 3; ++v) hv[(r * 3 + v) * FB_TJ + j] = a[v];
+    }
+    __syncthreads();
+    // along the columns, then the weights
+    for (int e = tid; e < ni * FB_TJ; e += 256) {
+        const int il = e / FB_TJ, j = e % FB_TJ;
+        if (j >= nj) continue;
         float t[9];
 #pragma unroll
         for (int k = 0; k < 9; ++k) t[k] = 0.f;
-        const float *db = dout + (size_t)b * H * W;
-        for (int Y = ylo; Y <= yhi; ++Y) {
-            const float wy = bilin_weight_to(Y, h, H, i);
-            if (wy == 0.f) continue;
-            for (int X = xlo; X <= xhi; ++X) {
-                const float wx = bilin_weight_to(X, w, W, j);
-                if (wx == 0.f) continue;
-                const float wgt = 256.0f * wy * wx;
+        const int r0 = ys[il] - R0 - 1;
 #pragma unroll
-                for (int u = 0; u < 3; ++u) {
-                    const int py = Y - (u - 1);
-                    if (py < 0 || py >= H) continue;
+        for (int k = 0; k < N; ++k) {
+            const float wk = 256.0f * wys[il * N + k];
+            if (wk == 0.f) continue;
 #pragma unroll
-                    for (int v = 0; v < 3; ++v) {
-                        const int px = X - (v - 1);
-                        if (px < 0 || px >= W) continue;
-                        t[u * 3 + v] += wgt * db[(size_t)py * W + px];
-                    }
-                }
-            }
+            for (int u = 0; u < 3; ++u)
+#pragma unroll
+                for (int v = 0; v < 3; ++v) t[u * 3 + v] += wk * hv[((r0 + k + 2 - u) * 3 + v) * FB_TJ + j];
         }
-        float *dt = dT + pix * 16;
+        const size_t pix = ((size_t)b * h + i0 + il) * w + j0 + j;
+        f32x4 *dt = (f32x4 *)(dT + pix * FB_DT);
+        dt[0] = f32x4{t[0], t[1], t[2], t[3]};
+        dt[1] = f32x4{t[4], t[5], t[6], t[7]};
+        dt[2] = f32x4{t[8], 0.f, 0.f, 0.f};
+        const typename Elem<DT>::T *g0 = G0 + pix * c1;
+        for (int c = 0; c < c1; c += 4) {
+            f32x4 r;
 #pragma unroll
-        for (int k = 0; k < 16; ++k) dt[k] = k < 9 ? t[k] : 0.f;
-        const float *wf = (const float *)wF;  // the final projection is always packed in FP32
-        const typename Elem<DT>::T *g0 = (const typename Elem<DT>::T *)G0 + pix * c1;
-        for (int c = 0; c < c1; ++c) {
-            float s = 0.f;
+            for (int q = 0; q < 4; ++q) {
+                float sum = 0.f;
 #pragma unroll
-            for (int k = 0; k < 9; ++k) s += wf[(size_t)k * wf_pitch + c] * t[k];
-            dpre0[pix * c1 + c] = s * (Elem<DT>::load(g0 + c) > 0.f ? 1.f : 0.1f);
+                for (int k = 0; k < 9; ++k) sum += wF[(size_t)k * wf_pitch + c + q] * t[k];
+                r[q] = sum * (Elem<DT>::load(g0 + c + q) > 0.f ? 1.f : 0.1f);
+            }
+            *(f32x4 *)(dpre0 + pix * c1 + c) = r;
         }
     }
+}
+
+template <int DT, int F>
+static void launch_final_bwd_f(const float *dout, int B, int H, int W, int h, int w, int f, const void *wF, int wf_pitch,
+                               int c1, const void *G0, float *dT, float *dpre0, float *sum_part, hipStream_t st) {
+    const int ti = fb_ti(f), n = 2 * F + 1;
+    const int sr = fb_span(ti, f), sc = fb_span(FB_TJ, f);
+    const size_t lds = sizeof(float) * ((size_t)sr * sc + sr * 3 * FB_TJ + FB_TJ * n + 8 * n + FB_TJ + 8 + 4);
+    hipLaunchKernelGGL((k_final_bwd<DT, F>), dim3(cdiv(w, FB_TJ), cdiv(h, ti), B), dim3(256), lds, st, dout, H, W, h, w,
+                       ti, sr, sc, (const float *)wF, wf_pitch, c1, (const typename Elem<DT>::T *)G0, dT, dpre0,
+                       sum_part);
+}
+
+// tiles of k_final_bwd: its entries of sum_part
+static size_t final_bwd_tiles(int B, int h, int w, int f) { return (size_t)B * cdiv(h, fb_ti(f)) * cdiv(w, FB_TJ); }
+
+static sv_status launch_final_bwd(int dtype, const float *dout, int B, int H, int W, int h, int w, int f, const void *wF,
+                                  int wf_pitch, int c1, const void *G0, float *dT, float *dpre0, float *sum_part,
+                                  hipStream_t st) {
+    if (cdiv(h, fb_ti(f)) > 65535 || B > 65535) return SV_ERR_SHAPE;
+#define SV_FB(D)                                                                                                       \
+    case D:                                                                                                            \
+        if (f <= 2) launch_final_bwd_f<D, 2>(dout, B, H, W, h, w, f, wF, wf_pitch, c1, G0, dT, dpre0, sum_part, st);     \
+        else if (f <= 4) launch_final_bwd_f<D, 4>(dout, B, H, W, h, w, f, wF, wf_pitch, c1, G0, dT, dpre0, sum_part, st); \
+        else launch_final_bwd_f<D, 8>(dout, B, H, W, h, w, f, wF, wf_pitch, c1, G0, dT, dpre0, sum_part, st);            \
+        break;
+    switch (dtype) {
+        SV_FB(SV_F32)
+        SV_FB(SV_BF16)
+        SV_FB(SV_F16)
+    default: return SV_ERR_DTYPE;
+    }
+#undef SV_FB
+    SV_LAUNCH_CHECK("k_final_bwd");
+    return SV_OK;
 }
 
 // Reparameterisation and KL adjoint: from dz to d[mu | logvar].
@@ -174,35 +326,21 @@ __global__ void k_latent_bwd(const float *__restrict__ dz, const float *__restri
     }
 }
 
-// Deterministic sum (fixed grid, fixed tree) of scale * x[0..n) into *out.
-constexpr int SUM_BLOCKS = 256;
-__global__ void __launch_bounds__(256) k_sum_partial(const float *__restrict__ x, int64_t n,
-                                                     float *__restrict__ part)
+// scale * the sum of x[0..n) into *out, in a fixed order: one workgroup, each
+// thread a strided run in FP64, then a tree.
+__global__ void __launch_bounds__(1024) k_sum_final(const float *__restrict__ x, int n, float scale,
+                                                    float *__restrict__ out)
 {
-    __shared__ float sh[256];
-    const int64_t per = (n + gridDim.x - 1) / gridDim.x;
-    const int64_t lo = blockIdx.x * per, hi = lo + per < n ? lo + per : n;
-    float s = 0.f;
-    for (int64_t i = lo + threadIdx.x; i < hi; i += 256) s += x[i];
-    sh[threadIdx.x] = s;
+    __shared__ double sh[1024];
+    double t = 0.0;
+    for (int i = threadIdx.x; i < n; i += 1024) t += x[i];
+    sh[threadIdx.x] = t;
     __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-        if (threadIdx.x < k) sh[threadIdx.x] += sh[threadIdx.x + k];
+    for (int k = 512; k > 0; k >>= 1) {
+        if ((int)threadIdx.x < k) sh[threadIdx.x] += sh[threadIdx.x + k];
         __syncthreads();
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
-}
-__global__ void __launch_bounds__(256) k_sum_final(const float *__restrict__ part, float scale,
-                                                   float *__restrict__ out)
-{
-    __shared__ float sh[256];
-    sh[threadIdx.x] = threadIdx.x < SUM_BLOCKS ? part[threadIdx.x] : 0.f;
-    __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-        if (threadIdx.x < k) sh[threadIdx.x] += sh[threadIdx.x + k];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = scale * sh[0];
+    if (threadIdx.x == 0) *out = (float)(scale * sh[0]);
 }
 
 // ---------------------------------------------------------------------------
@@ -240,7 +378,7 @@ static BwdLayout bwd_layout(const NetShape &ns, const Levels &lv, int B) {
     const int c1 = ns.c1, c2 = ns.c2, c3 = ns.c3, L = ns.L;
     size_t o = 0;
     auto take = [&](size_t floats) { size_t r = o; o = align256(o + floats * sizeof(float)); return r; };
-    l.dT = take(px(0) * 16);
+    l.dT = take(px(0) * FB_DT);
     l.dpre0 = take(px(0) * c1);
     l.dG1up = take(px(0) * c1);
     l.dpre1 = take(px(1) * c1);
@@ -253,7 +391,7 @@ static BwdLayout bwd_layout(const NetShape &ns, const Levels &lv, int B) {
     l.dpreE3 = take(px(3) * c3);
     l.dpreE2 = take(px(2) * c2);
     l.dpreE1 = take(px(1) * c1);
-    l.sum = take(SUM_BLOCKS);
+    l.sum = take(final_bwd_tiles(B, lv.h[0], lv.w[0], ns.f));
     // the partial sums of the largest weight gradient (layers run one after another)
     size_t mx = 0;
     for (int li = 0; li < NLAYERS; ++li) mx = std::max(mx, wgrad_part_floats(wgrad_job(ns, lv, B, li)));
@@ -362,30 +500,14 @@ sv_status net_backward(const NetShape &ns, const void *packed, const void *saved
 
     // ---- final layer -----------------------------------------------------------------
     {
-        const size_t n = (size_t)B * h[0] * wd[0];
-        const int blocks = (int)((n + 255) / 256 < 8192 ? (n + 255) / 256 : 8192);
-        const void *wF = (const char *)packed + ns.w_off[L_F];
-        switch (dt) {
-#define SV_FB(D)                                                                                    \
-        case D:                                                                                     \
-            hipLaunchKernelGGL(k_final_bwd<D>, dim3(blocks), dim3(256), 0, st, dout, H, W, h[0],    \
-                               wd[0], B, wF, ns.cin_pad[L_F], c1, G0, F(bl.dT), F(bl.dpre0));      \
-            break;
-            SV_FB(SV_F32)
-            SV_FB(SV_BF16)
-            SV_FB(SV_F16)
-#undef SV_FB
-        default: return SV_ERR_DTYPE;
-        }
-        SV_LAUNCH_CHECK("k_final_bwd");
+        SV_TRY(launch_final_bwd(dt, dout, B, H, W, h[0], wd[0], ns.f, (const char *)packed + ns.w_off[L_F],
+                                ns.cin_pad[L_F], c1, G0, F(bl.dT), F(bl.dpre0), F(bl.sum), st));
         // dW_F from X = [G0, x0] and dT (a 1x1 layer with the 9 taps as outputs), in FP32
-        SV_TRY(wgrad(L_F, bsrc(G0, SRC_TENSOR, c1, c1, 0, h[0], wd[0], 1 + dt), x0, F(bl.dT), 16));
+        SV_TRY(wgrad(L_F, bsrc(G0, SRC_TENSOR, c1, c1, 0, h[0], wd[0], 1 + dt), x0, F(bl.dT), FB_DT));
         // db_F = 256 * sum(dout)
-        hipLaunchKernelGGL(k_sum_partial, dim3(SUM_BLOCKS), dim3(256), 0, st, dout,
-                           (int64_t)B * H * W, F(bl.sum));
-        hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(256), 0, st, F(bl.sum), 256.0f,
-                           gl[L_F] + 9 * (c1 + 2));
-        SV_LAUNCH_CHECK("k_sum");
+        hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(1024), 0, st, F(bl.sum),
+                           (int)final_bwd_tiles(B, h[0], wd[0], ns.f), 256.0f, gl[L_F] + 9 * (c1 + 2));
+        SV_LAUNCH_CHECK("k_sum_final");
     }
 
     // ---- G0: input [resize(G1), x0] at level 0 -------------------------------------

@@ -46,6 +46,7 @@ struct sv_batch_plan {
     int dsplit;
     int cen_th;  // census tile height (4 or 16)
     int fin_th;  // final gather tile height (16, 32 or 64)
+    int g0_th;   // rows a tile of G0's own kernel, 0: the general one
     int cfg[NLAYERS];
     int grid[BS_NSTAGES];
     size_t cap[4];
@@ -218,6 +219,7 @@ static void pair_tiles(const sv_batch_plan *pl, const PairGeo &g, int *tiles) {
         tiles[r.stage] = conv_tiles(pl->cfg[r.li], g.h[r.out_level], g.w[r.out_level],
                                     run_cout(pl->ns, r.li));
     tiles[BS_E1] = enc1_tiles(g.h[1], g.w[1]);  // E1 runs as a direct stencil
+    if (pl->g0_th) tiles[BS_G0] = cdiv(g.w[0], 16) * cdiv(g.h[0], pl->g0_th);
     // the final layer: the gather's tiles when G0 projects, else k_final's
     const int final_tile_h = net_projects(pl->ns, false) ? pl->fin_th : FIN_TILE_H;
     tiles[BS_FINAL] = cdiv(g.W, FIN_TILE_W) * cdiv(g.H, final_tile_h);
@@ -289,8 +291,11 @@ static sv_status enqueue_stages(sv_batch_plan *pl, const void *packed, hipStream
             p.proj_scale0 = x0.scale0;
         }
         const int ks = li == L_F ? 1 : ns.ly[li].k, stride = li == L_F ? 1 : ns.ly[li].stride;
-        r = launch_conv_tab(li == L_F ? SV_F32 : ns.dtype, ks, stride, pl->cfg[li], p,
-                            pl->grid[run.stage], st);
+        if (li == L_G0 && pl->g0_th)
+            r = launch_g0(ns.dtype, pl->g0_th, p, pl->grid[run.stage], st);
+        else
+            r = launch_conv_tab(li == L_F ? SV_F32 : ns.dtype, ks, stride, pl->cfg[li], p,
+                                pl->grid[run.stage], st);
         if (r != SV_OK) return r;
     }
     if (net_projects(ns, false))
@@ -372,6 +377,8 @@ sv_status sv_batch_plan_create(const sv_vae_desc *desc, int max_n, int max_H, in
             pl->cfg[i] = ov >= 0 ? ov : cfg[i];
         }
     }
+    if (net_projects(ns, false) && g0_fits(ns.dtype, ns.c1))
+        pl->g0_th = g0_tile_h(pl->cfg[L_G0] % conv_num_tiles());
     for (int i = 0; i < L_F; ++i)
         pl->cfg[i] = conv_resolve_cfg(ns.dtype, ns.ly[i].k, ns.ly[i].stride, conv_persistent_cfg(pl->cfg[i]));
     if (net_projects(ns, false)) pl->cfg[L_G0] = net_g0_proj_cfg(ns, pl->cfg[L_G0]);

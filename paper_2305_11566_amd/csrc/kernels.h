@@ -295,6 +295,14 @@ sv_status launch_final_gather_tab(const PairTable *tab, int grid, const float *T
 // whether a conv tile configuration can carry the projection epilogue for a
 // layer with cout output channels (one channel tile, all of it in each wave)
 bool conv_cfg_projects(int cfg, int cout);
+// G0 with the projection epilogue as a kernel of its own (g0.hip): p as for
+// launch_conv with proj_out set, src[0] the resized level below (its storage
+// dtype, pitch = C), src[1] x0.  g0_fits: the dtypes and channel counts it
+// takes; g0_tile_h: its rows a tile for configuration cfg; grid > 0: persistent
+// over p.tab's tiles of stage p.stage.
+bool g0_fits(int dtype, int c1);
+int g0_tile_h(int cfg);
+sv_status launch_g0(int dtype, int th, const ConvParams &p, int grid, hipStream_t s);
 // the tile shape for a 3x3 layer of this size that nothing was tuned for
 int conv_default_tile(int dtype, int stride, int cin, int cout, int B, int Ho, int Wo);
 // the configuration a persistent pair-table launch runs for cfg

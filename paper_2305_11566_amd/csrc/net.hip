@@ -420,7 +420,8 @@ sv_status net_forward(const NetShape &ns, const void *packed, const uint8_t *dis
             p.proj_disp = disp;
             p.proj_img = img;
             p.proj_scale0 = (float)ns.f / 256.0f;
-            SV_STAGE(launch_conv(ns.dtype, 3, 1, net_g0_proj_cfg(ns, cfg[L_G0]), p, st));
+            if (g0_fits(ns.dtype, c1)) SV_STAGE(launch_g0(ns.dtype, g0_tile_h(cfg[L_G0] % conv_num_tiles()), p, 0, st));
+            else SV_STAGE(launch_conv(ns.dtype, 3, 1, net_g0_proj_cfg(ns, cfg[L_G0]), p, st));
         }
         ev_rec(8, 1, st);
     } else {

@@ -367,7 +367,16 @@ sv_status sv_batch_plan_create(const sv_vae_desc *desc, int max_n, int max_H, in
     pl->dsplit = cost_wta_split_for(max_n, mx.h[0], mx.w[0], max_D);
     pl->cen_th = census_tile_height(max_n, mx.h[0], mx.w[0]);
     pl->fin_th = gather_tile_h(ns.f, (long long)max_n * max_H * max_W);
-    for (int i = 0; i < NLAYERS; ++i) pl->cfg[i] = net_default_cfg(ns, i, mx, max_n);
+    for (int i = 0; i < NLAYERS; ++i) {
+        pl->cfg[i] = net_default_cfg(ns, i, mx, max_n);
+        // FP32 plans stay with four rows where single calls take more: the
+        // persistent kernels keep fewer workgroups of a taller FP32 tile on a
+        // CU (25 pairs up to 839x225: the three decoder layers 173 against 184 us)
+        int th, tn;
+        conv_cfg_tile(pl->cfg[i], th, tn);
+        if (ns.dtype == SV_F32 && i < L_F && th > 4 && net_get_cfg_override(ns.dtype, i) < 0)
+            pl->cfg[i] = ns.ly[i].cout <= 32 ? 2 /* th4_tn32 */ : 0 /* th4_tn64 */;
+    }
     int ds;
     int cfg[NLAYERS];
     if (tuned_lookup(ns, max_n, max_H, max_W, cfg, &ds)) {

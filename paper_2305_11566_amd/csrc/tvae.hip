@@ -24,7 +24,7 @@
 #include <mutex>
 #include <tuple>
 
-#include "kernels.h"
+#include "mfma.h"
 
 namespace sv {
 
@@ -139,7 +139,7 @@ TvLevels tv_levels(int f, int H, int W) {
     return lv;
 }
 
-struct TvAct { size_t L1, L2, L3, Z, ML, T, part, part_bytes, total; };
+struct TvAct { size_t L1, L2, L3, Z, ML, part, part_bytes, total; };
 
 // output level of each launched layer
 constexpr int kOutLevel[T_NL] = {1, 2, 2, 3, 3, 3, 3, 3, 2, 2, 1, 1};
@@ -159,7 +159,6 @@ TvAct tv_act(int es, const TvLevels &lv, int B) {
     a.L3 = o; o = align256(o + px(3) * L3C * es);
     a.Z = o;  o = align256(o + px(3) * ZC * es);
     a.ML = o; o = align256(o + px(3) * 2 * sizeof(float));
-    a.T = o;  o = align256(o + px(1) * TC * sizeof(float));
     a.part = o; o = align256(o + a.part_bytes);
     a.total = o;
     return a;
@@ -267,28 +266,186 @@ __global__ void k_tv_reparam(const float *__restrict__ ml, const float *__restri
     for (int c = 1; c < ZC; ++c) o[c] = Elem<DT>::make(0.f);
 }
 
-// out[b][y][x] = 256 * (bias + sum over level-1 pixels (i, j) and taps (u, v)
-// with f*i + u - 2 = y, f*j + v - 2 = x of T[b][i][j][5u + v]), rows i and
-// columns j ascending.
-__global__ void __launch_bounds__(256)
-k_tv_final(const float *__restrict__ T, int B, int h, int w, int f, int H, int W,
-           const float *__restrict__ bias, float *__restrict__ out) {
-    const int x = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int y = blockIdx.y * 4 + (threadIdx.x >> 6);
-    const int b = blockIdx.z;
-    if (x >= W || y >= H) return;
-    // i with 0 <= y + 2 - f i <= 4
-    const int ilo = max(0, (y - 2 + f - 1 + 2 * f) / f - 2), ihi = min(h - 1, (y + 2) / f);
-    const int jlo = max(0, (x - 2 + f - 1 + 2 * f) / f - 2), jhi = min(w - 1, (x + 2) / f);
-    float s = 0.f;
-    for (int i = ilo; i <= ihi; ++i) {
-        const int u = y + 2 - f * i;
-        for (int j = jlo; j <= jhi; ++j) {
-            const int v = x + 2 - f * j;
-            s += T[(((size_t)b * h + i) * w + j) * TC + u * TV_K + v];
+// The upsampling layer: the 25 tap projections T[t] = w[t] . [D | FE | x0] of
+// each level-1 pixel (FP32 weights, FP32 matrix steps, the map as stored) and
+//   out[b][y][x] = 256 * (bias + sum over level-1 pixels (i, j) and taps (u, v)
+//   with f*i + u - 2 = y, f*j + v - 2 = x of T[i][j][5u + v]), rows i and
+//   columns j ascending,
+// in one kernel.  It is bound by reading the map (160 bytes a pixel in 16 bits)
+// and writing the result; the projections stay in LDS, where storing them cost
+// 128 bytes a pixel written and read again.  A workgroup makes the outputs of
+// 16 x 8 level-1 pixels from the projections of these and of the HL before /
+// HH after them that an output's five taps reach, 16 pixels at a time on a wave:
+// lane group g multiplies channels 20 g .. 20 g + 19, five loads of four channels
+// straight from the map, and the weights stay in registers for all of a
+// workgroup's tiles.  BF16 maps take three BF16 steps of 32 channels in place of
+// eight FP32 steps of 4, the weight as the sum of three parts (24 bits; against
+// 64 bits its error is two thirds of the FP32 steps'): 52 -> 33 us.
+// Two kernels before: 16 BF16 images of 1242x375 125 -> 33 us, one in FP32 14.3
+// -> 9.2, 4 of 512x256 at factor 2 in FP32 34 -> 20.
+constexpr int TF_TW = 16, TF_TH = 8;
+
+template <int F>  // the factor; 0: any from 3
+struct FinalTile {
+    static constexpr int HL = F == 1 ? 2 : F == 2 ? 1 : 0, HH = F == 1 ? 2 : 1;
+    static constexpr int PW = TF_TW + HL + HH, PH = TF_TH + HL + HH, NPIX = PW * PH;
+    static constexpr int NG = (NPIX + 15) / 16;
+    // plane pitch: a step's four lane groups write 16 banks apart
+    static constexpr int PITCH = (NG * 16 + 43) / 64 * 64 + 20;
+};
+
+template <int DT, int F>
+__global__ void __launch_bounds__(256, 4)
+k_tv_final(const typename Elem<DT>::T *__restrict__ L1, const uint8_t *__restrict__ disp,
+           const uint8_t *__restrict__ img, float scale0, const float *__restrict__ wpk, int cin_pad,
+           const float *__restrict__ bias, int h, int w, int f_any, int H, int W, int tiles_x, int tiles_y, int tiles,
+           float *__restrict__ out) {
+    using G = FinalTile<F>;
+    using ST = typename Elem<DT>::T;
+    typedef ST S4 __attribute__((ext_vector_type(4)));
+    // BF16: the FP32 weight is the sum of three BF16 parts (24 bits)
+    constexpr bool SPLIT = DT == SV_BF16;
+    const int f = F ? F : f_any;
+    __shared__ float T[TV_TAPS * G::PITCH];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int g = lane >> 4, r16 = lane & 15;
+    // this lane's weights: tap 16 n + r16, channels 20 g .. 20 g + 19; x0's two (groups 0, 1)
+    float ax[2];
+    float af[SPLIT ? 1 : 2][20];
+    u16x8 as[SPLIT ? 2 : 1][3][3];  // [block][eight channels][part]
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        const float *wr = wpk + (size_t)(16 * n + r16) * cin_pad;
+        ax[n] = g < 2 ? wr[80 + g] : 0.f;
+#pragma unroll
+        for (int i = 0; i < (SPLIT ? 24 : 20); ++i) {
+            if constexpr (!SPLIT) {
+                af[n][i] = wr[20 * g + i];
+            } else {
+                float v = i < 20 ? wr[20 * g + i] : 0.f;
+#pragma unroll
+                for (int p = 0; p < 3; ++p) {
+                    const ST q = Elem<DT>::make(v);
+                    as[n][i / 8][p][i % 8] = q;
+                    const float qf = Elem<DT>::load(&q);
+                    v = fabsf(qf) < INFINITY ? v - qf : 0.f;
+                }
+            }
         }
     }
-    out[((size_t)b * H + y) * W + x] = 256.0f * (s + bias[0]);
+    for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
+        const int b = t / (tiles_x * tiles_y), r = t - b * tiles_x * tiles_y;
+        const int i0 = r / tiles_x * TF_TH, j0 = r % tiles_x * TF_TW;
+        const size_t ib = (size_t)b * h * w;
+        // ---- projections ------------------------------------------------------
+        S4 x[5];
+        float x0 = 0.f;
+        auto load = [&](int grp) {
+            // (pixels outside the map are read at its edge and not used)
+            const int px = min(grp * 16 + r16, G::NPIX - 1), py = px / G::PW;
+            const int i = min(max(i0 - G::HL + py, 0), h - 1), j = min(max(j0 - G::HL + px - py * G::PW, 0), w - 1);
+            const size_t q = ib + (size_t)i * w + j;
+            const ST *s = L1 + q * L1C + 20 * g;
+#pragma unroll
+            for (int k = 0; k < 5; ++k) x[k] = *(const S4 *)(s + 4 * k);
+            const float v = (float)(g == 0 ? disp : img)[q];
+            x0 = g == 0 ? scale0 * v : v * (1.0f / 256.0f);
+        };
+        load(wave);
+        for (int grp = wave; grp < G::NG; grp += 4) {
+            // NS sums a block (shorter chains, of steps and of roundings)
+            constexpr int NS = SPLIT ? 2 : 4;
+            f32x4 c[2][NS];
+#pragma unroll
+            for (int k = 0; k < 2 * NS; ++k) c[k % 2][k / 2] = f32x4{0.f, 0.f, 0.f, 0.f};
+            const float x0c = x0;
+            if constexpr (SPLIT) {
+                u16x8 xb[3];
+#pragma unroll
+                for (int k = 0; k < 6; ++k)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) xb[k / 2][k % 2 * 4 + e] = k < 5 ? (uint16_t)x[k < 5 ? k : 0][e] : (uint16_t)0;
+                if (grp + 4 < G::NG) load(grp + 4);
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+#pragma unroll
+                    for (int p = 2; p >= 0; --p)
+#pragma unroll
+                        for (int n = 0; n < 2; ++n) {
+                            f32x4 &a = c[n][p == 0];
+                            a = Mfma<DT>::run(as[n][k][p], xb[k], a);
+                        }
+            } else {
+                float xv[20];
+#pragma unroll
+                for (int k = 0; k < 5; ++k)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) xv[4 * k + e] = Elem<DT>::load((const ST *)&x[k] + e);
+                if (grp + 4 < G::NG) load(grp + 4);
+#pragma unroll
+                for (int i = 0; i < 20; ++i)
+#pragma unroll
+                    for (int n = 0; n < 2; ++n) {
+                        f32x4 &a = c[n][i % NS];
+                        a = __builtin_amdgcn_mfma_f32_16x16x4f32(af[n][i], xv[i], a, 0, 0, 0);
+                    }
+            }
+#pragma unroll
+            for (int n = 0; n < 2; ++n) {
+                f32x4 s = c[n][0] + c[n][1];
+                if constexpr (NS == 4) s += c[n][2] + c[n][3];
+                s = __builtin_amdgcn_mfma_f32_16x16x4f32(ax[n], x0c, s, 0, 0, 0);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int tap = 16 * n + 4 * g + e;
+                    if (tap < TV_TAPS) T[tap * G::PITCH + grp * 16 + r16] = s[e];
+                }
+            }
+        }
+        __syncthreads();
+        // ---- gather -------------------------------------------------------------
+        const int ow = TF_TW * f, oh = TF_TH * f;
+        const float bv = bias[0];
+        for (int e = threadIdx.x; e < ow * oh; e += 256) {
+            const int oy = e / ow, ox = e - oy * ow;
+            const int y = i0 * f + oy, xx = j0 * f + ox;
+            if (y >= H || xx >= W) continue;
+            // i with 0 <= y + 2 - f i <= 4
+            const int ilo = max(0, (y - 2 + f - 1 + 2 * f) / f - 2), ihi = min(h - 1, (y + 2) / f);
+            const int jlo = max(0, (xx - 2 + f - 1 + 2 * f) / f - 2), jhi = min(w - 1, (xx + 2) / f);
+            float s = 0.f;
+            for (int i = ilo; i <= ihi; ++i) {
+                const int u = y + 2 - f * i;
+                for (int j = jlo; j <= jhi; ++j) {
+                    const int v = xx + 2 - f * j;
+                    s += T[(u * TV_K + v) * G::PITCH + (i - i0 + G::HL) * G::PW + j - j0 + G::HL];
+                }
+            }
+            out[((size_t)b * H + y) * W + xx] = 256.0f * (s + bv);
+        }
+        __syncthreads();
+    }
+}
+
+template <int DT>
+sv_status tv_final(const TvShape &s, const void *packed, const void *L1, const uint8_t *disp, const uint8_t *img,
+                   int B, int h, int w, int f, int H, int W, float *out, hipStream_t st) {
+    using ST = typename Elem<DT>::T;
+    const int tx = cdiv(w, TF_TW), ty = cdiv(h, TF_TH), tiles = B * tx * ty;
+    auto run = [&](auto *fn) {
+        const long long n = resident_grid((const void *)fn, 0, tiles);
+        hipLaunchKernelGGL(fn, dim3((unsigned)n), dim3(256), 0, st, (const ST *)L1, disp, img, (float)f / 256.0f,
+                           (const float *)((const char *)packed + s.w_off[T_YP]), s.cin_pad[T_YP],
+                           (const float *)((const char *)packed + s.b_off[T_YP]), h, w, f, H, W, tx, ty, tiles, out);
+    };
+    switch (f) {
+    case 1: run(k_tv_final<DT, 1>); break;
+    case 2: run(k_tv_final<DT, 2>); break;
+    case 4: run(k_tv_final<DT, 4>); break;
+    default: run(k_tv_final<DT, 0>); break;
+    }
+    SV_LAUNCH_CHECK("k_tv_final");
+    return SV_OK;
 }
 
 __global__ void k_tv_copy(const float *__restrict__ src, int n, float *__restrict__ dst) {
@@ -441,11 +598,10 @@ sv_status tv_layer(const TvShape &s, const void *packed, int li, ConvSrc s0, Con
     p.cin_pad = s.cin_pad[li];
     p.n_pad = s.n_pad[li];
     p.wpk = (const char *)packed + s.w_off[li];
-    p.bias = li == T_YP ? nullptr : (const float *)((const char *)packed + s.b_off[li]);
+    p.bias = (const float *)((const char *)packed + s.b_off[li]);
     p.out = out; p.out_pitch = out_pitch; p.out_coff = out_coff;
     p.act = act; p.out_f32 = out_f32;
-    const int dt = li == T_YP ? SV_F32 : s.dtype;
-    return launch_conv(dt, kLayers[li].k, kLayers[li].stride, cfg[li], p, st);
+    return launch_conv(s.dtype, kLayers[li].k, kLayers[li].stride, cfg[li], p, st);
 }
 
 sv_status tv_forward(const TvShape &s, int f, const void *packed, const uint8_t *disp, const uint8_t *img,
@@ -465,13 +621,9 @@ sv_status tv_forward(const TvShape &s, int f, const void *packed, const uint8_t 
     // mu / sigma stay in the workspace (the backward reads them there); the
     // caller's buffer gets a copy
     float *ML = (float *)(w + a.ML);
-    float *T = (float *)(w + a.T);
     float *part = (float *)(w + a.part);
     const int h1 = lv.h[1], w1 = lv.w[1], h2 = lv.h[2], w2 = lv.w[2], h3 = lv.h[3], w3 = lv.w[3];
     const ConvSrc none{};
-    ConvSrc x0{};
-    x0.ptr = disp; x0.img = img; x0.kind = SRC_X0; x0.C = 2; x0.hs = h1; x0.ws = w1;
-    x0.scale0 = (float)f / 256.0f;
     // feature extraction: [FE_1 | FE_2] into level 1, channels 16..79
     SV_TRY_STATUS(tv_fe(s, packed, disp, img, B, h1, w1, f, L1, cfg, only, st));
     // encoder
@@ -518,16 +670,12 @@ sv_status tv_forward(const TvShape &s, int f, const void *packed, const uint8_t 
     else
         SV_TRY_STATUS(tv_layer(s, packed, T_D, tsrc(L2, 48, L2C, 0, h2, w2, SRC_ZINS, 0), none, B, 2 * h2 - 1,
                                2 * w2 - 1, h1, w1, L1, L1C, 0, 0, 1, part, a.part_bytes, cfg, only, st));
-    // upsampling layer: tap projection of [D | FE_1 | FE_2 | X_0 X_1] (FP32
-    // weights; the map is read in its stored dtype), then the gather
-    const int sdt = s.dtype == SV_F32 ? 0 : 1 + s.dtype;
-    SV_TRY_STATUS(tv_layer(s, packed, T_YP, tsrc(L1, 80, L1C, 0, h1, w1, SRC_TENSOR, sdt), x0, B, h1, w1, h1, w1,
-                           T, TC, 0, 1, 0, part, a.part_bytes, cfg, only, st));
     if (only >= 0) return SV_OK;
-    hipLaunchKernelGGL(k_tv_final, dim3(cdiv(W, 64), cdiv(H, 4), B), dim3(256), 0, st, T, B, h1, w1, f, H, W,
-                       (const float *)((const char *)packed + s.b_off[T_YP]), out);
-    SV_LAUNCH_CHECK("k_tv_final");
-    return SV_OK;
+    switch (s.dtype) {
+    case SV_F32: return tv_final<SV_F32>(s, packed, L1, disp, img, B, h1, w1, f, H, W, out, st);
+    case SV_BF16: return tv_final<SV_BF16>(s, packed, L1, disp, img, B, h1, w1, f, H, W, out, st);
+    default: return tv_final<SV_F16>(s, packed, L1, disp, img, B, h1, w1, f, H, W, out, st);
+    }
 }
 
 // ---- backward ----------------------------------------------------------------------
@@ -1044,19 +1192,18 @@ sv_status sv_tvae_autotune(int dtype, int factor, int B, int H, int W) {
     }
     const int reps = B >= 16 ? 4 : 12;
     for (int li = 0; li < T_NL && r == SV_OK; ++li) {
-        if (li == T_FE) continue;  // a direct stencil, no tile configuration
-        const int dt = li == T_YP ? SV_F32 : dtype;
+        if (li == T_FE || li == T_YP) continue;  // kernels of their own, no tile configuration
         const int k = kOutLevel[li];
         const long long npix = (long long)B * lv.h[k] * lv.w[k];
         float bt = 1e30f;
         best[li] = base[li];
         for (int c = 0; c < conv_num_cfgs() && r == SV_OK; ++c) {
-            if (conv_resolve_cfg(dt, kLayers[li].k, kLayers[li].stride, c) != c) continue;
+            if (conv_resolve_cfg(dtype, kLayers[li].k, kLayers[li].stride, c) != c) continue;
             // a split the launch would not take duplicates a smaller one
             const int want = c / conv_num_tiles() + 1;
             static float dummy;
             const TvAct a = tv_act(s.es, lv, B);
-            if (conv_effective_split(dt, c, kLayers[li].cin, npix, s.n_pad[li], &dummy, a.part_bytes) != want) continue;
+            if (conv_effective_split(dtype, c, kLayers[li].cin, npix, s.n_pad[li], &dummy, a.part_bytes) != want) continue;
             cur[li] = c;
             const float t = timed(li, reps);
             if (t < bt) { bt = t; best[li] = c; }

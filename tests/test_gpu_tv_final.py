@@ -44,3 +44,35 @@ def test_upsampling_against_64_bits(dtype, H, W, f, B):
     want = 256 * (F.conv_transpose2d(cat, wy, stride=f, padding=2)[:, 0, :H, :W] + params[-1].double())
     err = float((out.double().cpu() - want).abs().max() / want.abs().max())
     assert err <= TOL_F32, f"normwise {err:.3e}"
+
+
+# FP32: a chain of 25 roundings and the bias, half a unit each; 16 bits: the
+# stored value's rounding on top
+FE_TOL = {"f32": 26 * 2.0 ** -24, "bf16": 2.0 ** -8, "f16": 2.0 ** -11}
+
+
+@pytest.mark.parametrize("h,w,f,B", [(1, 1, 4, 1), (5, 17, 2, 2), (45, 33, 3, 70), (16, 16, 1, 512)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_feature_extraction_against_64_bits(dtype, h, w, f, B):
+    """Four rows a workgroup and (from 512 workgroups) sixteen, remainders in both."""
+    import paper_2305_11566_amd as sv
+    rng = np.random.default_rng(h + w)
+    disp = torch.from_numpy(rng.integers(0, 60, (B, h, w)).astype(np.uint8))
+    img = torch.from_numpy(rng.integers(0, 256, (B, h, w)).astype(np.uint8))
+    net = sv.TableVAE(f, dtype)
+    es = ES[dtype]
+    # weights the dtype holds exactly: the layer's own error is left
+    params = torch.from_numpy(rng.normal(0, 0.1, net.nparams).astype(np.float32)).to(es).float()
+    net.pack(params.cuda())
+    net.forward(cuda(disp.numpy()), cuda(img.numpy()), h * f, w * f)
+    torch.cuda.synchronize()
+    l1 = net.workspace(B, h * f, w * f)[:B * h * w * 80 * es.itemsize].view(es).reshape(B, h, w, 80)
+    got = l1[..., 16:].double().cpu().permute(0, 3, 1, 2)
+    p = params.double()
+    want, size = [], []
+    for c, x in enumerate((disp.double() * f / 256, img.double() / 256)):
+        wt, bias = p[c * 832:c * 832 + 800].reshape(32, 1, 5, 5), p[c * 832 + 800:c * 832 + 832]
+        want.append(F.leaky_relu(F.conv2d(x[:, None], wt, bias, padding=2), 0.1))
+        size.append(F.conv2d(x[:, None], wt.abs(), bias.abs(), padding=2))
+    err = (got - torch.cat(want, 1)).abs()
+    assert float((err / torch.cat(size, 1)).max()) <= FE_TOL[dtype] + (26 * 2.0 ** -24)

@@ -602,11 +602,10 @@ sv_status sv_tvae_set_layer_cfg(int layer, int cfg);
 int sv_tvae_num_layers(void);
 
 /* Form of the two stride-2 deconvolutions (D_2, D) in sv_tvae_forward: -1
- * (default) by output size -- four polyphase 3x3 launches (one per output
- * parity class, over the un-inserted input) from 131072 output pixels, else
- * one 5x5 launch over the zero-inserted input; 0 always the zero-inserted
- * form; 1 always polyphase.  Both compute the same deconvolution (they differ
- * in FP32 summation order only).  Errors: SV_ERR_RANGE. */
+ * (default) the transposed convolution's own kernel; 0 one 5x5 convolution over
+ * the zero-inserted input (the same bits where its reduction is not split); 1
+ * four polyphase 3x3 launches (one per output parity class, over the un-inserted
+ * input; another FP32 summation order).  Errors: SV_ERR_RANGE. */
 sv_status sv_tvae_set_deconv_form(int form);
 
 /* Times every tile configuration of each launched layer of sv_tvae_forward

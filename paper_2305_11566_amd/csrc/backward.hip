@@ -3,10 +3,10 @@
 // reading documented in sv.h).
 //
 //   * input gradients (dgrad) reuse the forward implicit-GEMM kernel with the
-//     adjoint weight pack (rows = the layer's inputs, kernel flipped); the
-//     stride-2 encoder layers see the output gradient with zeros inserted
-//     (SRC_ZINS), and the epilogue adds the skip-connection gradient and
-//     multiplies by the leaky-ReLU derivative of the layer below;
+//     adjoint weight pack (rows = the layer's inputs, kernel flipped), those of
+//     the stride-2 encoder layers the transposed convolution (tconv.hip); the
+//     epilogue adds the skip-connection gradient and multiplies by the
+//     leaky-ReLU derivative of the layer below;
 //   * weight gradients (wgrad.hip) are an MFMA GEMM reducing over pixels: every
 //     workgroup owns a fixed slice of output tiles and writes its partial sums;
 //     a second kernel adds the partials in a fixed order (no float atomics), so
@@ -433,6 +433,7 @@ static sv_status dgrad(const NetShape &ns, const void *packed, int li, ConvSrc d
     p.add = add; p.add_pitch = add_pitch; p.add_coff = add_coff;
     p.mask = mask; p.mask_pitch = mask_pitch;
     const int ks = ns.ly[li].k;
+    if (dy.kind == SRC_ZINS) return launch_tconv(ns.dtype, ks, p, st);
     const int cfg = ks == 3 ? conv_default_tile(ns.dtype, 1, dy.C, cout_needed, B, Hi, Wi)
                             : (cout_needed <= 16 ? 5 : (cout_needed <= 32 ? 2 : 0));
     return launch_conv(ns.dtype, ks, 1, cfg, p, st);
@@ -546,7 +547,7 @@ sv_status net_backward(const NetShape &ns, const void *packed, const void *saved
     SV_TRY(wgrad(L_HEAD, T_(E3, c3, 3), none, F(bl.dML), 2 * L));
     SV_TRY(dgrad(ns, packed, L_HEAD, Gf(F(bl.dML), 2 * L, 2 * L, 3), B, h[3], wd[3], c3,
                  F(bl.dpreE3), c3, nullptr, 0, 0, E3, c3, st));
-    // ---- encoder (stride 2): input gradients through the zero-inserted view ------------
+    // ---- encoder (stride 2): input gradients by the transposed convolution -------------
     SV_TRY(wgrad(L_E3, T_(E2, c2, 2), none, F(bl.dpreE3), c3));
     SV_TRY(dgrad(ns, packed, L_E3, bsrc(F(bl.dpreE3), SRC_ZINS, c3, c3, 0, h[3], wd[3], SDT_F32), B, h[2],
                  wd[2], c2, F(bl.dpreE2), c2, F(bl.dcat2), c3 + c2, c3, E2, c2, st));

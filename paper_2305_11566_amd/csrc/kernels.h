@@ -303,6 +303,11 @@ bool conv_cfg_projects(int cfg, int cout);
 bool g0_fits(int dtype, int c1);
 int g0_tile_h(int cfg);
 sv_status launch_g0(int dtype, int th, const ConvParams &p, int grid, hipStream_t s);
+// A stride-2 transposed convolution of src[0], the map itself (tconv.hip):
+// the ks x ks correlation of its zero-inserted view, Ho x Wo outputs.  Weights,
+// bias, epilogue and bits as launch_conv over that view; ks 3 or 5, uniform
+// launches, whole groups of 8 channels stored in dtype or FP32.
+sv_status launch_tconv(int dtype, int ks, const ConvParams &p, hipStream_t s);
 // the tile shape for a 3x3 layer of this size that nothing was tuned for
 int conv_default_tile(int dtype, int stride, int cin, int cout, int B, int Ho, int Wo);
 // the configuration a persistent pair-table launch runs for cfg

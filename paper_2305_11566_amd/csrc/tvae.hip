@@ -11,12 +11,12 @@
 //   level 2 (h1/2):                     [D_2 16 | EN_1 16 | EN_1_R 8 | D_2_R 8] 48 ch
 //   level 3 (h1/4):                     [D_1 32 | EN_2 32 | EN_2_R 16 | D_1_R 16] 96 ch
 // A stride-2 deconvolution is a stride-1 convolution with the flipped kernel
-// over its input seen with zeros inserted between samples (SRC_ZINS), cut to
-// the size of the level it feeds.  FE_1 and FE_2 run as one layer over the two
+// over its input seen with zeros inserted between samples, cut to the size of
+// the level it feeds (tconv.hip computes it without the zeros).  FE_1 and FE_2 run as one layer over the two
 // input channels with block-diagonal weights.  The final upsampling layer
-// (5x5, stride f, one output channel) runs as a 1x1 projection of the level-1
-// map and X_0 onto its 25 taps (MFMA), then a gather that adds, for each
-// full-resolution pixel, the taps that land on it.
+// (5x5, stride f, one output channel) is a 1x1 projection of the level-1 map and
+// X_0 onto its 25 taps (MFMA) and a gather that adds, for each full-resolution
+// pixel, the taps that land on it, in one kernel.
 #include <algorithm>
 #include <array>
 #include <atomic>
@@ -459,17 +459,11 @@ ConvSrc tsrc(const void *p, int C, int pitch, int coff, int hs, int ws, int kind
     return s;
 }
 
-// Form of the stride-2 deconvolutions: -1 by output size (polyphase from
-// TV_PHASE_MIN_PIX output pixels: four launches beat one only when each has
-// enough work), 0 always over the zero-inserted grid, 1 always polyphase.
+// Form of the stride-2 deconvolutions: -1 their own kernel (k_tconv), 0 the
+// general convolution over the zero-inserted grid, 1 as four polyphase ones (a
+// pass of 16 BF16 images of 1242x375 261 us by the first against 341 by the
+// faster of the others for each layer, of one in FP32 136 against 148).
 std::atomic<int> g_tv_deconv_form{-1};
-constexpr long long TV_PHASE_MIN_PIX = 131072;
-
-bool tv_polyphase(int B, int Ho, int Wo) {
-    const int f = g_tv_deconv_form.load();
-    if (f >= 0) return f == 1;
-    return (long long)B * Ho * Wo >= TV_PHASE_MIN_PIX;
-}
 
 // Feature extraction (FE_1 = conv5x5(X_0), FE_2 = conv5x5(X_1), 32 outputs
 // each, leaky ReLU) into channels 16..79 of the level-1 map.  Bound by writing
@@ -598,33 +592,6 @@ sv_status tv_fe(const TvShape &s, const void *packed, const uint8_t *disp, const
     }
 }
 
-// A stride-2 deconvolution (D_2 or D) as four 3x3 correlations over its
-// input, one per output parity class, each writing its pixels of the
-// interleaved Ho x Wo output.
-sv_status tv_deconv2(const TvShape &s, const void *packed, int li, ConvSrc src, int B, int Hi, int Wi, int Ho,
-                     int Wo, void *out, int out_pitch, int out_coff, const int *cfg, int only, hipStream_t st) {
-    if (only >= 0 && only != li) return SV_OK;
-    for (int ph = 0; ph < 4; ++ph) {
-        const int py = ph >> 1, px = ph & 1;
-        ConvParams p{};
-        p.src[0] = src;
-        p.B = B; p.Hi = Hi; p.Wi = Wi;
-        p.Ho = (Ho - py + 1) / 2; p.Wo = (Wo - px + 1) / 2;
-        if (p.Ho <= 0 || p.Wo <= 0) continue;
-        p.ophase = 1 + ph; p.Ho_full = Ho; p.Wo_full = Wo;
-        p.Cin = src.C;
-        p.Cout = kLayers[li].cout;
-        p.cin_pad = s.cin_pad[li];
-        p.n_pad = s.n_pad[li];
-        p.wpk = (const char *)packed + s.ph_off[li][ph];
-        p.bias = (const float *)((const char *)packed + s.b_off[li]);
-        p.out = out; p.out_pitch = out_pitch; p.out_coff = out_coff;
-        p.act = 1;
-        SV_TRY_STATUS(launch_conv(s.dtype, 3, 1, cfg[li] % conv_num_tiles(), p, st));
-    }
-    return SV_OK;
-}
-
 // One launched layer with configuration cfg[li]; with only >= 0 every other
 // layer is skipped (the autotuner times one layer at a time).
 sv_status tv_layer(const TvShape &s, const void *packed, int li, ConvSrc s0, ConvSrc s1, int B, int Hi,
@@ -645,6 +612,54 @@ sv_status tv_layer(const TvShape &s, const void *packed, int li, ConvSrc s0, Con
     p.out = out; p.out_pitch = out_pitch; p.out_coff = out_coff;
     p.act = act; p.out_f32 = out_f32;
     return launch_conv(s.dtype, kLayers[li].k, kLayers[li].stride, cfg[li], p, st);
+}
+
+// A stride-2 deconvolution (D_2 or D) by the form that is set; the polyphase
+// one is four 3x3 correlations over its input, one per output parity class,
+// each writing its pixels of the interleaved Ho x Wo output.
+sv_status tv_deconv2(const TvShape &s, const void *packed, int li, ConvSrc src, int B, int Hi, int Wi, int Ho,
+                     int Wo, void *out, int out_pitch, int out_coff, float *part, size_t part_bytes, const int *cfg,
+                     int only, hipStream_t st) {
+    if (only >= 0 && only != li) return SV_OK;
+    const int form = g_tv_deconv_form.load();
+    if (form == 0) {
+        src.kind = SRC_ZINS;
+        return tv_layer(s, packed, li, src, ConvSrc{}, B, 2 * Hi - 1, 2 * Wi - 1, Ho, Wo, out, out_pitch, out_coff, 0,
+                        1, part, part_bytes, cfg, only, st);
+    }
+    if (form < 0) {
+        ConvParams p{};
+        p.src[0] = src;
+        p.B = B; p.Hi = 2 * Hi - 1; p.Wi = 2 * Wi - 1; p.Ho = Ho; p.Wo = Wo;
+        p.Cin = src.C;
+        p.Cout = kLayers[li].cout;
+        p.cin_pad = s.cin_pad[li];
+        p.n_pad = s.n_pad[li];
+        p.wpk = (const char *)packed + s.w_off[li];
+        p.bias = (const float *)((const char *)packed + s.b_off[li]);
+        p.out = out; p.out_pitch = out_pitch; p.out_coff = out_coff;
+        p.act = 1;
+        return launch_tconv(s.dtype, kLayers[li].k, p, st);
+    }
+    for (int ph = 0; ph < 4; ++ph) {
+        const int py = ph >> 1, px = ph & 1;
+        ConvParams p{};
+        p.src[0] = src;
+        p.B = B; p.Hi = Hi; p.Wi = Wi;
+        p.Ho = (Ho - py + 1) / 2; p.Wo = (Wo - px + 1) / 2;
+        if (p.Ho <= 0 || p.Wo <= 0) continue;
+        p.ophase = 1 + ph; p.Ho_full = Ho; p.Wo_full = Wo;
+        p.Cin = src.C;
+        p.Cout = kLayers[li].cout;
+        p.cin_pad = s.cin_pad[li];
+        p.n_pad = s.n_pad[li];
+        p.wpk = (const char *)packed + s.ph_off[li][ph];
+        p.bias = (const float *)((const char *)packed + s.b_off[li]);
+        p.out = out; p.out_pitch = out_pitch; p.out_coff = out_coff;
+        p.act = 1;
+        SV_TRY_STATUS(launch_conv(s.dtype, 3, 1, cfg[li] % conv_num_tiles(), p, st));
+    }
+    return SV_OK;
 }
 
 sv_status tv_forward(const TvShape &s, int f, const void *packed, const uint8_t *disp, const uint8_t *img,
@@ -697,22 +712,13 @@ sv_status tv_forward(const TvShape &s, int f, const void *packed, const uint8_t 
                            L3, L3C, 0, 0, 1, part, a.part_bytes, cfg, only, st));
     SV_TRY_STATUS(tv_layer(s, packed, T_D1R, tsrc(L3, 80, L3C, 0, h3, w3, SRC_TENSOR, 0), none, B, h3, w3, h3, w3,
                            L3, L3C, 80, 0, 1, part, a.part_bytes, cfg, only, st));
-    // stride-2 deconvolutions: polyphase for large outputs, else one launch over
-    // the zero-inserted grid (2n - 1 samples per axis)
-    if (tv_polyphase(B, h2, w2))
-        SV_TRY_STATUS(tv_deconv2(s, packed, T_D2, tsrc(L3, 96, L3C, 0, h3, w3, SRC_TENSOR, 0), B, h3, w3, h2, w2,
-                                 L2, L2C, 0, cfg, only, st));
-    else
-        SV_TRY_STATUS(tv_layer(s, packed, T_D2, tsrc(L3, 96, L3C, 0, h3, w3, SRC_ZINS, 0), none, B, 2 * h3 - 1,
-                               2 * w3 - 1, h2, w2, L2, L2C, 0, 0, 1, part, a.part_bytes, cfg, only, st));
+    // stride-2 deconvolutions
+    SV_TRY_STATUS(tv_deconv2(s, packed, T_D2, tsrc(L3, 96, L3C, 0, h3, w3, SRC_TENSOR, 0), B, h3, w3, h2, w2,
+                             L2, L2C, 0, part, a.part_bytes, cfg, only, st));
     SV_TRY_STATUS(tv_layer(s, packed, T_D2R, tsrc(L2, 40, L2C, 0, h2, w2, SRC_TENSOR, 0), none, B, h2, w2, h2, w2,
                            L2, L2C, 40, 0, 1, part, a.part_bytes, cfg, only, st));
-    if (tv_polyphase(B, h1, w1))
-        SV_TRY_STATUS(tv_deconv2(s, packed, T_D, tsrc(L2, 48, L2C, 0, h2, w2, SRC_TENSOR, 0), B, h2, w2, h1, w1,
-                                 L1, L1C, 0, cfg, only, st));
-    else
-        SV_TRY_STATUS(tv_layer(s, packed, T_D, tsrc(L2, 48, L2C, 0, h2, w2, SRC_ZINS, 0), none, B, 2 * h2 - 1,
-                               2 * w2 - 1, h1, w1, L1, L1C, 0, 0, 1, part, a.part_bytes, cfg, only, st));
+    SV_TRY_STATUS(tv_deconv2(s, packed, T_D, tsrc(L2, 48, L2C, 0, h2, w2, SRC_TENSOR, 0), B, h2, w2, h1, w1,
+                             L1, L1C, 0, part, a.part_bytes, cfg, only, st));
     if (only >= 0) return SV_OK;
     switch (s.dtype) {
     case SV_F32: return tv_final<SV_F32>(s, packed, L1, disp, img, B, h1, w1, f, H, W, out, st);
@@ -864,6 +870,7 @@ sv_status tv_dgrad(const TvShape &s, const void *packed, int li, ConvSrc dy, int
     p.wpk = (const char *)packed + s.bw_off[li];
     p.out = out; p.out_pitch = out_pitch; p.out_coff = out_coff; p.out_f32 = 1;
     if (add) { p.add = out; p.add_pitch = out_pitch; p.add_coff = out_coff; }
+    if (dy.kind == SRC_ZINS) return launch_tconv(s.dtype, kLayers[li].k, p, st);
     const int cfg = p.Cout <= 16 ? 5 : 2;
     return launch_conv(li == T_YP ? SV_F32 : s.dtype, kLayers[li].k, stride, cfg, p, st);
 }
@@ -964,7 +971,7 @@ sv_status tv_backward(const TvShape &s, int f, const void *packed, const uint8_t
     SV_TRY_STATUS(wgrad(T_EN2R, C_EN2R, tsrc(L3, 32, L3C, 32, h3, w3, SRC_TENSOR, 0), none, dL3 + 64, L3C));
     SV_TRY_STATUS(tv_dgrad(s, packed, T_EN2R, fsrc(dL3, 16, L3C, 64, h3, w3, SRC_TENSOR), 1, B, h3, w3, h3, w3,
                            dL3, L3C, 32, true, st));
-    // EN_2 (stride 2: its input gradient runs over the zero-inserted output gradient)
+    // EN_2 (stride 2: its input gradient is a transposed convolution)
     SV_TRY_STATUS(mask(dL3, L3C, 32, L3, L3C, 32, 32, p3));
     SV_TRY_STATUS(wgrad(T_EN2, C_EN2, tsrc(L2, 24, L2C, 16, h2, w2, SRC_TENSOR, 0), none, dL3 + 32, L3C));
     SV_TRY_STATUS(tv_dgrad(s, packed, T_EN2, fsrc(dL3, 32, L3C, 32, h3, w3, SRC_ZINS), 1, B, 2 * h3 - 1, 2 * w3 - 1,
@@ -1235,7 +1242,8 @@ sv_status sv_tvae_autotune(int dtype, int factor, int B, int H, int W) {
     }
     const int reps = B >= 16 ? 4 : 12;
     for (int li = 0; li < T_NL && r == SV_OK; ++li) {
-        if (li == T_FE || li == T_YP) continue;  // kernels of their own, no tile configuration
+        // kernels of their own, no tile configuration
+        if (li == T_FE || li == T_YP || ((li == T_D2 || li == T_D) && g_tv_deconv_form.load() < 0)) continue;
         const int k = kOutLevel[li];
         const long long npix = (long long)B * lv.h[k] * lv.w[k];
         float bt = 1e30f;

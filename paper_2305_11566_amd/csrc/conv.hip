@@ -45,6 +45,7 @@ static const CfgDesc kCfgs[] = {
 static constexpr int kNumTiles = (int)(sizeof(kCfgs) / sizeof(kCfgs[0]));
 static constexpr int kMaxSplit = CONV_MAX_SPLIT;
 static constexpr int kFallbackTile = 5;  // th4_tn16
+static constexpr int kTile4x32 = 2;      // th4_tn32
 int conv_num_tiles() { return kNumTiles; }
 int conv_num_cfgs() { return kNumTiles * kMaxSplit; }
 
@@ -160,6 +161,10 @@ sv_status launch_conv_split(int dtype, int ks, int stride, int cfg, const ConvPa
         p.ksplit = 1;
     }
     if (ksplit_used) *ksplit_used = p.ksplit > 1 ? p.ksplit : 1;
+    // 5x5 layers at the default tiles
+    const int tile = cfg % kNumTiles;
+    if ((ks == 3 || tile == kFallbackTile || tile == kTile4x32) && conv_rows_fits(dtype, ks, stride, p))
+        return launch_conv_rows(dtype, ks, stride, p, st);
     return launch_any(dtype, ks, stride, cfg % kNumTiles, p, 0, st);
 }
 

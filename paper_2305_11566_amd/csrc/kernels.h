@@ -308,6 +308,11 @@ sv_status launch_g0(int dtype, int th, const ConvParams &p, int grid, hipStream_
 // bias, epilogue and bits as launch_conv over that view; ks 3 or 5, uniform
 // launches, whole groups of 8 channels stored in dtype or FP32.
 sv_status launch_tconv(int dtype, int ks, const ConvParams &p, hipStream_t s);
+// An unsplit 3x3 or 5x5 convolution of one map read in place, or a 3x3 one of
+// [resize(map) | second source] (conv_rows.hip): weights, epilogue and bits as launch_conv.  conv_rows_fits:
+// the launches it takes.
+bool conv_rows_fits(int dtype, int ks, int stride, const ConvParams &p);
+sv_status launch_conv_rows(int dtype, int ks, int stride, const ConvParams &p, hipStream_t s);
 // the tile shape for a 3x3 layer of this size that nothing was tuned for
 int conv_default_tile(int dtype, int stride, int cin, int cout, int B, int Ho, int Wo);
 // the configuration a persistent pair-table launch runs for cfg

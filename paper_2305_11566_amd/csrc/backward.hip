@@ -432,6 +432,7 @@ static sv_status dgrad(const NetShape &ns, const void *packed, int li, ConvSrc d
     p.out = out; p.out_pitch = out_pitch; p.out_f32 = 1;
     p.add = add; p.add_pitch = add_pitch; p.add_coff = add_coff;
     p.mask = mask; p.mask_pitch = mask_pitch;
+    p.mask_lo = 0; p.mask_hi = cout_needed;
     const int ks = ns.ly[li].k;
     if (dy.kind == SRC_ZINS) return launch_tconv(ns.dtype, ks, p, st);
     const int cfg = ks == 3 ? conv_default_tile(ns.dtype, 1, dy.C, cout_needed, B, Hi, Wi)

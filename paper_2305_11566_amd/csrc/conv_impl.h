@@ -111,22 +111,51 @@ __device__ __forceinline__ float conv_epilogue(const ConvParams &p, size_t pix, 
     constexpr int DT = Store<DT0>::v;
     using T = typename Elem<DT>::T;
     float r[4];
+    const bool full = nbase + 4 <= p.Cout;
+    // the backward terms of the four channels (INT8 has none), by one load each where
+    // they lie aligned
+    constexpr bool BWD = DT0 != SV_I8;
+    float add[4] = {0.f, 0.f, 0.f, 0.f}, mv[4] = {1.f, 1.f, 1.f, 1.f};
+    if (BWD && p.add) {
+        const float *q = p.add + (pix * p.add_pitch + p.add_coff + nbase);
+        if (full && (uintptr_t)q % 16 == 0) {
+            const f32x4 v = *(const f32x4 *)q;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) add[i] = v[i];
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (nbase + i < p.Cout) add[i] = q[i];
+        }
+    }
+    if (BWD && p.mask && nbase + 4 > p.mask_lo && nbase < p.mask_hi) {
+        typedef T T4 __attribute__((ext_vector_type(4)));
+        const T *q = (const T *)p.mask + (pix * p.mask_pitch + nbase);
+        if (p.mask_sdt) {  // a 16-bit map beside an FP32 launch
+            const uint16_t *q16 = (const uint16_t *)p.mask + (pix * p.mask_pitch + nbase);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (nbase + i >= p.mask_lo && nbase + i < p.mask_hi)
+                    mv[i] = p.mask_sdt == 1 + SV_BF16 ? Elem<SV_BF16>::load(q16 + i) : Elem<SV_F16>::load(q16 + i);
+        } else if (nbase >= p.mask_lo && nbase + 4 <= p.mask_hi && (uintptr_t)q % sizeof(T4) == 0) {
+            const T4 v = *(const T4 *)q;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) mv[i] = Elem<DT>::load((const T *)&v + i);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (nbase + i >= p.mask_lo && nbase + i < p.mask_hi) mv[i] = Elem<DT>::load(q + i);
+        }
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int n = nbase + i;
         float val = acc[i] + bias[i];
         if (p.act) val = val > 0.f ? val : 0.1f * val;
-        if (n < p.Cout) {
-            if (p.add) val += p.add[pix * p.add_pitch + p.add_coff + n];
-            if (p.mask) {
-                const float mv = Elem<DT>::load((const T *)p.mask + pix * p.mask_pitch + n);
-                val *= mv > 0.f ? 1.0f : 0.1f;
-            }
-        }
+        if (BWD && p.add) val += add[i];
+        if (BWD && p.mask) val *= mv[i] > 0.f ? 1.0f : 0.1f;
         r[i] = val;
     }
     const size_t o = pix * p.out_pitch + p.out_coff + nbase;
-    const bool full = nbase + 4 <= p.Cout;
     float amax = 0.f;
     if (p.out_f32) {
         float *op = (float *)p.out + o;

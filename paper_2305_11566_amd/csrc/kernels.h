@@ -102,8 +102,10 @@ struct ConvParams {
     // optional epilogue terms of the backward pass, on the output grid:
     const float *add;    // += add[pix * add_pitch + add_coff + n] (FP32)
     int add_pitch, add_coff;
-    const void *mask;    // *= (mask[pix * mask_pitch + n] > 0 ? 1 : 0.1), compute dtype
-    int mask_pitch;
+    const void *mask;    // *= (mask[pix * mask_pitch + n] > 0 ? 1 : 0.1), compute dtype,
+    int mask_pitch;      // for channels mask_lo <= n < mask_hi <= Cout
+    int mask_lo, mask_hi;
+    int mask_sdt;        // 0: stored in the compute dtype, else 1 + SV_BF16 / SV_F16
     // pair-table mode (persistent over the tiles of all pairs); NULL = uniform batch
     const PairTable *tab;
     int stage, in_level, out_level;

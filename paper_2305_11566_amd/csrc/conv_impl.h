@@ -131,13 +131,7 @@ __device__ __forceinline__ float conv_epilogue(const ConvParams &p, size_t pix, 
     if (BWD && p.mask && nbase + 4 > p.mask_lo && nbase < p.mask_hi) {
         typedef T T4 __attribute__((ext_vector_type(4)));
         const T *q = (const T *)p.mask + (pix * p.mask_pitch + nbase);
-        if (p.mask_sdt) {  // a 16-bit map beside an FP32 launch
-            const uint16_t *q16 = (const uint16_t *)p.mask + (pix * p.mask_pitch + nbase);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (nbase + i >= p.mask_lo && nbase + i < p.mask_hi)
-                    mv[i] = p.mask_sdt == 1 + SV_BF16 ? Elem<SV_BF16>::load(q16 + i) : Elem<SV_F16>::load(q16 + i);
-        } else if (nbase >= p.mask_lo && nbase + 4 <= p.mask_hi && (uintptr_t)q % sizeof(T4) == 0) {
+        if (nbase >= p.mask_lo && nbase + 4 <= p.mask_hi && (uintptr_t)q % sizeof(T4) == 0) {
             const T4 v = *(const T4 *)q;
 #pragma unroll
             for (int i = 0; i < 4; ++i) mv[i] = Elem<DT>::load((const T *)&v + i);

@@ -105,7 +105,6 @@ struct ConvParams {
     const void *mask;    // *= (mask[pix * mask_pitch + n] > 0 ? 1 : 0.1), compute dtype,
     int mask_pitch;      // for channels mask_lo <= n < mask_hi <= Cout
     int mask_lo, mask_hi;
-    int mask_sdt;        // 0: stored in the compute dtype, else 1 + SV_BF16 / SV_F16
     // pair-table mode (persistent over the tiles of all pairs); NULL = uniform batch
     const PairTable *tab;
     int stage, in_level, out_level;

@@ -831,6 +831,50 @@ __global__ void __launch_bounds__(256) k_tv_sum_final(const float *__restrict__ 
     if (threadIdx.x == 0) out[0] = (float)(scale * sh[0]);
 }
 
+// The upsampling layer's input gradient: dL1[pixel][c] = sum over the 25 taps of
+// w[c][t] dT[pixel][t] for the 80 level-1 channels, D's (0..15) then through its
+// leaky ReLU.  Bound by writing the gradient map (320 bytes a pixel): 16 pixels
+// at a time on a wave, their taps (eight to a lane group) straight from memory
+// into FP32 matrix steps, all 80 channels of a pixel from one read, the weights
+// in registers for all of a wave's pixels.  4 maps of 256x128: 28 us, where the
+// general kernel took 36 (three channel tiles, each staging the taps again).
+template <int DT>
+__global__ void __launch_bounds__(256)
+k_tv_final_dgrad(const float *__restrict__ dT, const float *__restrict__ wpk, int cin_pad,
+                 const typename Elem<DT>::T *__restrict__ L1, int64_t npix, float *__restrict__ dL1) {
+    typedef typename Elem<DT>::T T4 __attribute__((ext_vector_type(4)));
+    constexpr int NB = L1C / 16;
+    const int lane = threadIdx.x & 63, g = lane >> 4, r16 = lane & 15;
+    float a[NB][8];  // channel 16 n + r16, tap 8 g + i
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            a[n][i] = 8 * g + i < TV_TAPS ? wpk[(16 * n + r16) * cin_pad + 8 * g + i] : 0.f;
+    const int64_t step = (int64_t)gridDim.x * 4 * 16;
+    for (int64_t p0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 16; p0 < npix; p0 += step) {
+        const int64_t px = p0 + r16, q = px < npix ? px : npix - 1;
+        const f32x4 x0 = *(const f32x4 *)(dT + q * TC + 8 * g), x1 = *(const f32x4 *)(dT + q * TC + 8 * g + 4);
+        const T4 act = *(const T4 *)(L1 + q * L1C + 4 * g);
+        f32x4 c[NB];
+#pragma unroll
+        for (int n = 0; n < NB; ++n) c[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int n = 0; n < NB; ++n)
+                c[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[n][i], i < 4 ? x0[i % 4] : x1[i % 4], c[n], 0, 0, 0);
+        if (px >= npix) continue;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float v = Elem<DT>::load((const typename Elem<DT>::T *)&act + i);
+            c[0][i] *= v > 0.f ? 1.0f : 0.1f;
+        }
+#pragma unroll
+        for (int n = 0; n < NB; ++n) *(f32x4 *)(dL1 + px * L1C + 16 * n + 4 * g) = c[n];
+    }
+}
+
 // Eq. (8) backward: d mu = dz (+ the loss's), d sigma = dz * eps * exp(sigma - 1) (+ the loss's)
 __global__ void k_tv_reparam_bwd(const float *__restrict__ dz, const float *__restrict__ ml, const float *__restrict__ eps,
                                  const float *__restrict__ dms, int n, float *__restrict__ dml) {
@@ -870,10 +914,9 @@ sv_status tv_dgrad(const TvShape &s, const void *packed, int li, ConvSrc dy, int
     if (add) { p.add = out; p.add_pitch = out_pitch; p.add_coff = out_coff; }
     p.mask = mask_hi ? (const char *)act + (size_t)out_coff * s.es : nullptr;
     p.mask_pitch = out_pitch; p.mask_lo = mask_lo; p.mask_hi = mask_hi;
-    if (li == T_YP && s.dtype != SV_F32) p.mask_sdt = 1 + s.dtype;  // (that launch is FP32)
     if (dy.kind == SRC_ZINS) return launch_tconv(s.dtype, kLayers[li].k, p, st);
     const int cfg = p.Cout <= 16 ? 5 : 2;
-    return launch_conv(li == T_YP ? SV_F32 : s.dtype, kLayers[li].k, stride, cfg, p, st);
+    return launch_conv(s.dtype, kLayers[li].k, stride, cfg, p, st);
 }
 
 sv_status tv_backward(const TvShape &s, int f, const void *packed, const uint8_t *disp, const uint8_t *img, int B,
@@ -890,7 +933,7 @@ sv_status tv_backward(const TvShape &s, int f, const void *packed, const uint8_t
     float *dZ = (float *)(bw + l.dZ), *dML = (float *)(bw + l.dML), *dT = (float *)(bw + l.dT);
     float *part = (float *)(bw + l.part), *sum = (float *)(bw + l.sum);
     const int h1 = lv.h[1], w1 = lv.w[1], h2 = lv.h[2], w2 = lv.w[2], h3 = lv.h[3], w3 = lv.w[3];
-    const size_t p1 = (size_t)B * h1 * w1, p2 = (size_t)B * h2 * w2, p3 = (size_t)B * h3 * w3;
+    const size_t p1 = (size_t)B * h1 * w1, p3 = (size_t)B * h3 * w3;
     const int sdt = s.dtype == SV_F32 ? 0 : 1 + s.dtype;  // the maps' storage, seen from an FP32 launch
     const ConvSrc none{};
     ConvSrc x0{};
@@ -924,8 +967,19 @@ sv_status tv_backward(const TvShape &s, int f, const void *packed, const uint8_t
     hipLaunchKernelGGL(k_tv_sum_final, dim3(1), dim3(256), 0, st, sum, 256.0f, grad + canon_off(C_Y) + 81 * 25);
     SV_LAUNCH_CHECK("k_tv_sum");
     SV_TRY_STATUS(wgrad(T_YP, C_Y, tsrc(L1, 80, L1C, 0, h1, w1, SRC_TENSOR, sdt), x0, dT, TC));
-    SV_TRY_STATUS(tv_dgrad(s, packed, T_YP, fsrc(dT, TV_TAPS, TC, 0, h1, w1, SRC_TENSOR), 1, B, h1, w1, h1, w1,
-                           dL1, L1C, 0, false, L1, 0, 16, st));
+    {
+        const float *wy = (const float *)((const char *)packed + s.bw_off[T_YP]);
+        auto run = [&](auto *fn, auto *act) {
+            const long long n = resident_grid((const void *)fn, 0, (long long)((p1 + 63) / 64));
+            hipLaunchKernelGGL(fn, dim3((unsigned)n), dim3(256), 0, st, dT, wy, s.bcin_pad[T_YP], act, (int64_t)p1, dL1);
+        };
+        switch (s.dtype) {
+        case SV_F32: run(k_tv_final_dgrad<SV_F32>, (const float *)L1); break;
+        case SV_BF16: run(k_tv_final_dgrad<SV_BF16>, (const uint16_t *)L1); break;
+        default: run(k_tv_final_dgrad<SV_F16>, (const uint16_t *)L1); break;
+        }
+        SV_LAUNCH_CHECK("k_tv_final_dgrad");
+    }
     // D (deconvolution into level 1)
     SV_TRY_STATUS(wgrad(T_D, C_D, fsrc(dL1, 16, L1C, 0, h1, w1, SRC_TENSOR), none, L2, L2C));
     SV_TRY_STATUS(tv_dgrad(s, packed, T_D, fsrc(dL1, 16, L1C, 0, h1, w1, SRC_TENSOR), 2, B, h1, w1, h2, w2,

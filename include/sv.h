@@ -602,7 +602,8 @@ sv_status sv_tvae_set_layer_cfg(int layer, int cfg);
 int sv_tvae_num_layers(void);
 
 /* Form of the two stride-2 deconvolutions (D_2, D) in sv_tvae_forward: -1
- * (default) the transposed convolution's own kernel; 0 one 5x5 convolution over
+ * (default) the transposed convolution's own kernel (16-bit layers whose
+ * configuration splits the reduction: form 0); 0 one 5x5 convolution over
  * the zero-inserted input (the same bits where its reduction is not split); 1
  * four polyphase 3x3 launches (one per output parity class, over the un-inserted
  * input; another FP32 summation order).  Errors: SV_ERR_RANGE. */

@@ -628,7 +628,14 @@ sv_status tv_deconv2(const TvShape &s, const void *packed, int li, ConvSrc src, 
                      int Wo, void *out, int out_pitch, int out_coff, float *part, size_t part_bytes, const int *cfg,
                      int only, hipStream_t st) {
     if (only >= 0 && only != li) return SV_OK;
-    const int form = g_tv_deconv_form.load();
+    int form = g_tv_deconv_form.load();
+    // 16-bit maps of small grids, whose zero-inserted launch splits its reduction,
+    // keep it: without the split the FP32 sums round otherwise, and the stored maps
+    // with them (3e-5 of the refined map of one 228x218 image)
+    if (form < 0 && s.dtype != SV_F32 &&
+        conv_effective_split(s.dtype, conv_resolve_cfg(s.dtype, kLayers[li].k, 1, cfg[li]), src.C,
+                             (long long)B * Ho * Wo, s.n_pad[li], part, part_bytes) > 1)
+        form = 0;
     if (form == 0) {
         src.kind = SRC_ZINS;
         return tv_layer(s, packed, li, src, ConvSrc{}, B, 2 * Hi - 1, 2 * Wi - 1, Ho, Wo, out, out_pitch, out_coff, 0,

@@ -42,3 +42,26 @@ def test_deconvolutions_equal_zero_inserted_bitwise(dtype, h, w, B):
         for layer in range(sv.sv_tvae_num_layers()):
             sv.sv_tvae_set_layer_cfg(layer, -1)
     assert np.array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_small_16_bit_grids_keep_their_split(dtype):
+    """Where the layers' configurations split the reduction, 16-bit passes take the
+    zero-inserted form by default too."""
+    import paper_2305_11566_amd as sv
+    rng = np.random.default_rng(11)
+    h, w = 40, 52
+    disp = cuda(rng.integers(0, 48, (1, h, w)).astype(np.uint8))
+    img = cuda(rng.integers(0, 256, (1, h, w)).astype(np.uint8))
+    net = sv.TableVAE(1, dtype)
+    net.pack(cuda(rng.normal(0, 0.05, net.nparams).astype(np.float32)))
+    outs = []
+    try:
+        for form in (0, -1):
+            sv.sv_tvae_set_deconv_form(form)
+            out, _ = net.forward(disp, img, h, w)
+            torch.cuda.synchronize()
+            outs.append(out.cpu().numpy())
+    finally:
+        sv.sv_tvae_set_deconv_form(-1)
+    assert np.array_equal(outs[0], outs[1])

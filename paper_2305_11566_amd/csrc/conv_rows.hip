@@ -285,7 +285,7 @@ int rows_of(int dtype, int ks, int stride, const ConvParams &p) {
     if (wgs(1) >= (1ll << 31)) return 0;
     if (stride == 1 && wgs(4) >= 256) return 4;
     if (wgs(2) >= 200) return 2;
-    return dtype == SV_F32 && wgs(1) >= (ks == 5 ? 48 : 128) ? 1 : 0;
+    return dtype == SV_F32 && wgs(1) >= 128 ? 1 : 0;
 }
 
 template <int DT, int KS, int S, int NB>

@@ -180,14 +180,7 @@ std::map<std::tuple<int, int, int, int, int>, std::array<int, T_NL>> g_tv_tuned;
 // gives 200, 5 us at batch 16); grids of fewer than 256
 // workgroups (the coarse levels of small batches) split the reduction over
 // up to four channel ranges so that more CUs take part.
-int tv_heuristic_cfg(int dtype, int layer, int B, int Ho, int Wo) {
-    // FP32 5x5 layers: the row kernel unsplit (one 1242x375 image: EN_1's 120
-    // workgroups 19 us, split over three ranges and summed 26; D_2_R's 12 and 15;
-    // EN_2's 60 9 and 12), but not with few workgroups or many channels in turn
-    // (EN_2_R's 30 10.2 and 9.7; D_1_R's 30 and 80 channels 19 and 13.5)
-    if (dtype == SV_F32 && kLayers[layer].k == 5 && kLayers[layer].cin <= 64 &&
-        (long long)cdiv(Wo, 16) * cdiv(Ho, 4) * B * cdiv(kLayers[layer].cout, 16) >= 48)
-        return 5 /* th4_tn16 */;
+int tv_heuristic_cfg(int layer, int B, int Ho, int Wo) {
     const int tn = kLayers[layer].cout <= 16 ? 16 : 32;
     const int tile = tn == 16 ? 5 /* th4_tn16 */ : 2 /* th4_tn32 */;
     const long long nwg = (long long)cdiv(Wo, 16) * cdiv(Ho, 4) * B * cdiv(kLayers[layer].cout, tn);
@@ -214,7 +207,7 @@ void tv_layer_cfgs(int dtype, int f, int B, int H, int W, int *cfg) {
     for (int i = 0; i < T_NL; ++i) {
         const int ov = g_tv_cfg[i].load();
         const int k = kOutLevel[i];
-        cfg[i] = (ov >= 0 && ov < conv_num_cfgs()) ? ov : (have ? tuned[i] : tv_heuristic_cfg(dtype, i, B, lv.h[k], lv.w[k]));
+        cfg[i] = (ov >= 0 && ov < conv_num_cfgs()) ? ov : (have ? tuned[i] : tv_heuristic_cfg(i, B, lv.h[k], lv.w[k]));
     }
 }
 
@@ -1279,7 +1272,7 @@ sv_status sv_tvae_autotune(int dtype, int factor, int B, int H, int W) {
     };
     for (int i = 0; i < T_NL; ++i) {
         const int k = kOutLevel[i];
-        base[i] = tv_heuristic_cfg(dtype, i, B, lv.h[k], lv.w[k]);
+        base[i] = tv_heuristic_cfg(i, B, lv.h[k], lv.w[k]);
         best[i] = cur[i] = base[i];
     }
     const int reps = B >= 16 ? 4 : 12;

@@ -280,7 +280,7 @@ __global__ void k_tv_reparam(const float *__restrict__ ml, const float *__restri
 // straight from the map, and the weights stay in registers for all of a
 // workgroup's tiles.  BF16 maps take three BF16 steps of 32 channels in place of
 // eight FP32 steps of 4, the weight as the sum of three parts (24 bits; against
-// 64 bits its error is two thirds of the FP32 steps'): 52 -> 33 us.
+// 64 bits its error is below the FP32 steps'): 52 -> 33 us.
 // Two kernels before: 16 BF16 images of 1242x375 125 -> 33 us, one in FP32 14.3
 // -> 9.2, 4 of 512x256 at factor 2 in FP32 34 -> 20.
 constexpr int TF_TW = 16, TF_TH = 8;

@@ -307,7 +307,10 @@ sv_status launch_g0(int dtype, int th, const ConvParams &p, int grid, hipStream_
 // A stride-2 transposed convolution of src[0], the map itself (tconv.hip):
 // the ks x ks correlation of its zero-inserted view, Ho x Wo outputs.  Weights,
 // bias, epilogue and bits as launch_conv over that view; ks 3 or 5, uniform
-// launches, whole groups of 8 channels stored in dtype or FP32.
+// launches, whole groups of 8 channels stored in dtype or FP32.  tconv_fits: the
+// launches it takes; others (an image's map of 2^31 elements) run as launch_conv
+// over the view.
+bool tconv_fits(int dtype, int ks, const ConvParams &p);
 sv_status launch_tconv(int dtype, int ks, const ConvParams &p, hipStream_t s);
 // An unsplit 3x3 or 5x5 convolution of one map read in place, or a 3x3 one of
 // [resize(map) | second source] (conv_rows.hip): weights, epilogue and bits as launch_conv.  conv_rows_fits:

@@ -215,13 +215,18 @@ sv_status launch_d(int ks, const ConvParams &p, hipStream_t st) {
 
 }  // namespace
 
-sv_status launch_tconv(int dtype, int ks, const ConvParams &p, hipStream_t st) {
+// The map is read in vectors of four elements of its own dtype, in whole channel
+// groups, at 32-bit offsets from an image's first element.
+bool tconv_fits(int dtype, int ks, const ConvParams &p) {
     const ConvSrc &s = p.src[0];
-    // the map read in vectors of four elements of its own dtype, whole channel groups
-    if ((ks != 3 && ks != 5) || p.src[1].kind != SRC_NONE || s.C % 8 || s.pitch % 4 || s.coff % 4 ||
-        (s.sdt && s.sdt - 1 != dtype && s.sdt - 1 != SV_F32) || p.Cin != s.C || p.Ho > 2 * s.hs || p.Wo > 2 * s.ws ||
-        (long long)s.hs * s.ws * s.pitch >= (1ll << 31))
-        return SV_ERR_UNSUPPORTED;
+    return (dtype == SV_F32 || dtype == SV_BF16 || dtype == SV_F16) && (ks == 3 || ks == 5) &&
+           p.src[1].kind == SRC_NONE && s.C % 8 == 0 && s.pitch % 4 == 0 && s.coff % 4 == 0 &&
+           (!s.sdt || s.sdt - 1 == dtype || s.sdt - 1 == SV_F32) && p.Cin == s.C && p.Ho <= 2 * s.hs &&
+           p.Wo <= 2 * s.ws && (long long)s.hs * s.ws * s.pitch < (1ll << 31);
+}
+
+sv_status launch_tconv(int dtype, int ks, const ConvParams &p, hipStream_t st) {
+    if (!tconv_fits(dtype, ks, p)) return SV_ERR_UNSUPPORTED;
     switch (dtype) {
     case SV_F32: return launch_d<SV_F32>(ks, p, st);
     case SV_BF16: return launch_d<SV_BF16>(ks, p, st);

@@ -629,11 +629,6 @@ sv_status tv_deconv2(const TvShape &s, const void *packed, int li, ConvSrc src, 
         conv_effective_split(s.dtype, conv_resolve_cfg(s.dtype, kLayers[li].k, 1, cfg[li]), src.C,
                              (long long)B * Ho * Wo, s.n_pad[li], part, part_bytes) > 1)
         form = 0;
-    if (form == 0) {
-        src.kind = SRC_ZINS;
-        return tv_layer(s, packed, li, src, ConvSrc{}, B, 2 * Hi - 1, 2 * Wi - 1, Ho, Wo, out, out_pitch, out_coff, 0,
-                        1, part, part_bytes, cfg, only, st);
-    }
     if (form < 0) {
         ConvParams p{};
         p.src[0] = src;
@@ -646,7 +641,13 @@ sv_status tv_deconv2(const TvShape &s, const void *packed, int li, ConvSrc src, 
         p.bias = (const float *)((const char *)packed + s.b_off[li]);
         p.out = out; p.out_pitch = out_pitch; p.out_coff = out_coff;
         p.act = 1;
-        return launch_tconv(s.dtype, kLayers[li].k, p, st);
+        if (tconv_fits(s.dtype, kLayers[li].k, p)) return launch_tconv(s.dtype, kLayers[li].k, p, st);
+        form = 0;
+    }
+    if (form == 0) {
+        src.kind = SRC_ZINS;
+        return tv_layer(s, packed, li, src, ConvSrc{}, B, 2 * Hi - 1, 2 * Wi - 1, Ho, Wo, out, out_pitch, out_coff, 0,
+                        1, part, part_bytes, cfg, only, st);
     }
     for (int ph = 0; ph < 4; ++ph) {
         const int py = ph >> 1, px = ph & 1;
@@ -914,7 +915,7 @@ sv_status tv_dgrad(const TvShape &s, const void *packed, int li, ConvSrc dy, int
     if (add) { p.add = out; p.add_pitch = out_pitch; p.add_coff = out_coff; }
     p.mask = mask_hi ? (const char *)act + (size_t)out_coff * s.es : nullptr;
     p.mask_pitch = out_pitch; p.mask_lo = mask_lo; p.mask_hi = mask_hi;
-    if (dy.kind == SRC_ZINS) return launch_tconv(s.dtype, kLayers[li].k, p, st);
+    if (dy.kind == SRC_ZINS && tconv_fits(s.dtype, kLayers[li].k, p)) return launch_tconv(s.dtype, kLayers[li].k, p, st);
     const int cfg = p.Cout <= 16 ? 5 : 2;
     return launch_conv(s.dtype, kLayers[li].k, stride, cfg, p, st);
 }

@@ -65,3 +65,24 @@ def test_small_16_bit_grids_keep_their_split(dtype):
     finally:
         sv.sv_tvae_set_deconv_form(-1)
     assert np.array_equal(outs[0], outs[1])
+
+
+def test_maps_past_32_bit_offsets_take_the_general_kernel():
+    """From 2^31 elements an image's map is past the kernel's offsets (level 2 of one
+    13400x13400 image at factor 1): the pass runs, as the zero-inserted form does."""
+    import paper_2305_11566_amd as sv
+    H = W = 13400
+    assert 48 * (H // 2) * (W // 2) >= 2 ** 31
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    disp = torch.randint(0, 48, (1, H, W), dtype=torch.uint8, device="cuda", generator=gen)
+    img = torch.randint(0, 256, (1, H, W), dtype=torch.uint8, device="cuda", generator=gen)
+    net = sv.TableVAE(1, "bf16")
+    net.pack(cuda(np.random.default_rng(3).normal(0, 0.05, net.nparams).astype(np.float32)))
+    out, _ = net.forward(disp, img, H, W)
+    try:
+        sv.sv_tvae_set_deconv_form(0)
+        want, _ = net.forward(disp, img, H, W)
+    finally:
+        sv.sv_tvae_set_deconv_form(-1)
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)

@@ -294,6 +294,27 @@ struct FinalTile {
     static constexpr int PITCH = (NG * 16 + 43) / 64 * 64 + 20;
 };
 
+// An output's sum straight from the maps in FP32 products, for one that the weight's
+// parts leave not finite: a part that is zero or of the other sign makes NaN of an
+// infinity of the map, and the first part of a weight past the largest BF16 value is
+// an infinity itself.
+template <int DT>
+__device__ __forceinline__ float tv_final_sum(const typename Elem<DT>::T *__restrict__ L1, const uint8_t *__restrict__ disp,
+                                              const uint8_t *__restrict__ img, float scale0, const float *__restrict__ wpk,
+                                              int cin_pad, size_t ib, int h, int w, int f, int y, int x) {
+    float s = 0.f;
+    for (int i = max(0, (y - 2 + 3 * f - 1) / f - 2); i <= min(h - 1, (y + 2) / f); ++i)
+        for (int j = max(0, (x - 2 + 3 * f - 1) / f - 2); j <= min(w - 1, (x + 2) / f); ++j) {
+            const size_t q = ib + (size_t)i * w + j;
+            const float *wr = wpk + ((y + 2 - f * i) * TV_K + x + 2 - f * j) * cin_pad;
+            float t = fmaf(wr[81], (float)img[q] * (1.0f / 256.0f), wr[80] * (scale0 * (float)disp[q]));
+#pragma unroll 1
+            for (int c = 0; c < L1C; ++c) t = fmaf(wr[c], Elem<DT>::load(L1 + q * L1C + c), t);
+            s += t;
+        }
+    return s;
+}
+
 template <int DT, int F>
 __global__ void __launch_bounds__(256, 4)
 k_tv_final(const typename Elem<DT>::T *__restrict__ L1, const uint8_t *__restrict__ disp,
@@ -333,6 +354,7 @@ k_tv_final(const typename Elem<DT>::T *__restrict__ L1, const uint8_t *__restric
             }
         }
     }
+    bool odd = false;  // (BF16) one of this thread's sums is not finite
     for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
         const int b = t / (tiles_x * tiles_y), r = t - b * tiles_x * tiles_y;
         const int i0 = r / tiles_x * TF_TH, j0 = r % tiles_x * TF_TW;
@@ -421,9 +443,26 @@ k_tv_final(const typename Elem<DT>::T *__restrict__ L1, const uint8_t *__restric
                     s += T[(u * TV_K + v) * G::PITCH + (i - i0 + G::HL) * G::PW + j - j0 + G::HL];
                 }
             }
+            if (SPLIT) odd |= !(fabsf(s) < INFINITY);
             out[((size_t)b * H + y) * W + xx] = 256.0f * (s + bv);
         }
         __syncthreads();
+    }
+    if constexpr (SPLIT) {
+        if (!odd) return;
+        // every thread's own outputs again (here, where the weights' registers are free)
+        for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
+            const int b = t / (tiles_x * tiles_y), r = t - b * tiles_x * tiles_y;
+            const int i0 = r / tiles_x * TF_TH, j0 = r % tiles_x * TF_TW;
+            const int ow = TF_TW * f, oh = TF_TH * f;
+            for (int e = threadIdx.x; e < ow * oh; e += 256) {
+                const int y = i0 * f + e / ow, x = j0 * f + e % ow;
+                if (y >= H || x >= W) continue;
+                float *o = out + ((size_t)b * H + y) * W + x;
+                if (fabsf(*o) < INFINITY) continue;
+                *o = 256.0f * (tv_final_sum<DT>(L1, disp, img, scale0, wpk, cin_pad, (size_t)b * h * w, h, w, f, y, x) + bias[0]);
+            }
+        }
     }
 }
 

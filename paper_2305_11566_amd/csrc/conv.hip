@@ -46,6 +46,7 @@ static constexpr int kNumTiles = (int)(sizeof(kCfgs) / sizeof(kCfgs[0]));
 static constexpr int kMaxSplit = CONV_MAX_SPLIT;
 static constexpr int kFallbackTile = 5;  // th4_tn16
 static constexpr int kTile4x32 = 2;      // th4_tn32
+static constexpr int kTile4x64 = 0;      // th4_tn64
 int conv_num_tiles() { return kNumTiles; }
 int conv_num_cfgs() { return kNumTiles * kMaxSplit; }
 
@@ -225,7 +226,7 @@ int conv_persistent_cfg(int cfg) {
 // where half the products would be padding.  INT8 keeps to 32 channels, its
 // accumulators and staging registers allow two workgroups a CU there (G2 at
 // batch 64 101 against 118 us, E2 50 against 62).
-int conv_default_tile(int dtype, int stride, int cin, int cout, int B, int Ho, int Wo) {
+static int rule_tile(int dtype, int stride, int cin, int cout, int B, int Ho, int Wo) {
     enum { T4_64 = 0, T8_64 = 1, T4_32 = 2, T8_32 = 3, T2_64 = 4, T4_16 = 5, T4_16_K4 = 6, T4_32_K2 = 7, T4_16_K2 = 8,
            T2_32_K2 = 11, T16_32 = 16 };
     constexpr long long kEnough = 400;
@@ -249,6 +250,14 @@ int conv_default_tile(int dtype, int stride, int cin, int cout, int B, int Ho, i
     if (wgs(2, 64) >= kEnough) return f32 && wgs(4, 32) >= 4 * kEnough ? T4_32 : T2_64;
     if (cin >= 64 && wgs(2, 64) >= kEnough / 2) return T2_64;
     return f32 || cin >= 64 ? T2_32_K2 : T4_16;
+}
+
+// Batches whose images times channel tiles pass a grid's 65535 planes in a narrow
+// tile take the widest.
+int conv_default_tile(int dtype, int stride, int cin, int cout, int B, int Ho, int Wo) {
+    const int t = rule_tile(dtype, stride, cin, cout, B, Ho, Wo);
+    if ((long long)B * cdiv(cout, kCfgs[t].TN) <= CONV_MAX_PLANES) return t;
+    return cout <= 16 ? kFallbackTile : (cout <= 32 ? kTile4x32 : kTile4x64);
 }
 
 bool conv_cfg_projects(int cfg, int cout) {

@@ -1080,7 +1080,7 @@ static sv_status launch_one(const ConvParams &p, int pgrid, hipStream_t st) {
     }
     const int ksplit = p.ksplit > 1 ? p.ksplit : 1;
     const long long gz = (long long)p.B * cdiv(p.Cout, TN) * ksplit;
-    if (gz > 65535) return SV_ERR_SHAPE;
+    if (gz > CONV_MAX_PLANES) return SV_ERR_SHAPE;
     dim3 grid(cdiv(p.Wo, 16), cdiv(p.Ho, TH), (unsigned)gz);
     if constexpr (DT == SV_I8 && TH == 16 && S == 1)
         hipLaunchKernelGGL((k_conv_w2<DT, KS, S, TH, TN, WM, KCM>), grid, dim3(256), 0, st, p);

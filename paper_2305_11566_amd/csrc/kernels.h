@@ -167,6 +167,8 @@ void conv_cfg_tile(int cfg, int &TH, int &TN);
 int conv_resolve_cfg(int dtype, int ks, int stride, int cfg);
 int conv_num_tiles();  // tile shapes; cfg = tile + conv_num_tiles() * (ksplit - 1)
 constexpr int CONV_MAX_SPLIT = 4;
+// images x channel tiles x split of a uniform launch
+constexpr int CONV_MAX_PLANES = 65535;
 // the split a launch of configuration cfg actually uses (1 when it cannot split)
 int conv_effective_split(int dtype, int cfg, int Cin, long long npix, int n_pad, const float *part,
                          size_t part_bytes);

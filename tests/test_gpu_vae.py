@@ -269,3 +269,16 @@ def test_many_tile_batch_equals_single_images(dtype):
     if dtype == "f32":
         t = vae.forward(params, disp, img, f, H, W)
         assert normwise(a, t["out"]) <= TOL_F32
+
+
+@pytest.mark.parametrize("dtype,C,B", [("f32", (8, 16, 128), 20000), ("i8", (16, 40, 64), 40000)])
+def test_batches_of_many_small_images(dtype, C, B):
+    """Batches whose images times channel tiles pass a grid's 65535 planes in tiles
+    narrower than 64 channels: every image is that of a single call."""
+    rng = np.random.default_rng(72)
+    disp = rng.integers(0, 48, (1, 8, 8)).astype(np.uint8)
+    img = rng.integers(0, 256, (1, 8, 8)).astype(np.uint8)
+    params = vae_params(C, 8, 7003)
+    one, _ = _gpu_forward(C, 8, 1, dtype, params, disp, img, 8, 8)
+    many, _ = _gpu_forward(C, 8, 1, dtype, params, np.repeat(disp, B, 0), np.repeat(img, B, 0), 8, 8)
+    assert (many == one).all()

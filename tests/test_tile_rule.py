@@ -30,3 +30,19 @@ def test_larger_grids_take_taller_tiles(monkeypatch, tmp_path):
     monkeypatch.setenv("SV_AUTOTUNE_CACHE", str(tmp_path / "none.tsv"))
     rows = [int(_names((32, 64, 128), 128, 4, "bf16", B, 375, 1242)[7][2:].split("_")[0]) for B in (1, 2, 4, 64)]
     assert rows == [4, 8, 16, 16]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16", "i8"])
+@pytest.mark.parametrize("c,latent", [((8, 8, 128), 8), ((16, 64, 64), 64), ((40, 96, 256), 128), ((72, 136, 200), 8)])
+def test_large_batches_keep_within_a_grid(monkeypatch, tmp_path, dtype, c, latent):
+    """Images times channel tiles of a launch are at most 65535: a batch that 64
+    channels a tile (or all of a narrower layer's) can take is taken by the rule's."""
+    monkeypatch.setenv("SV_AUTOTUNE_CACHE", str(tmp_path / "none.tsv"))
+    c1, c2, c3 = c
+    cout = (c1, c2, c3, 2 * latent, c3, c2, c1, c1)
+    for H, W in ((8, 8), (30, 33), (128, 128)):
+        for B in (10000, 16384, 20000, 21846, 32768, 50000, 65535):
+            for n, co in zip(_names(c, latent, 1, dtype, B, H, W), cout):
+                tn = int(n.split("_tn")[1].split("_")[0])
+                if B * -(-co // 64) <= 65535:
+                    assert B * -(-co // tn) <= 65535, (n, co, B, H, W)

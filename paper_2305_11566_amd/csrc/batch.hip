@@ -369,13 +369,15 @@ sv_status sv_batch_plan_create(const sv_vae_desc *desc, int max_n, int max_H, in
     pl->fin_th = gather_tile_h(ns.f, (long long)max_n * max_H * max_W);
     for (int i = 0; i < NLAYERS; ++i) {
         pl->cfg[i] = net_default_cfg(ns, i, mx, max_n);
-        // FP32 plans stay with four rows where single calls take more: the
-        // persistent kernels keep fewer workgroups of a taller FP32 tile on a
-        // CU (25 pairs up to 839x225: the three decoder layers 173 against 184 us)
+        // FP32 plans stay with four rows where single calls take more of 64 channels:
+        // the persistent kernels keep fewer workgroups of that tile on a CU (24 pairs of
+        // 512x256 at factor 2, layers of 64, 96 and 160 channels: 1262 against 1386 us a
+        // call; 16 of 640x384, the 1242x375 network: 593 against 628).  32 channels
+        // gain by the rows as single calls do (64 pairs to 1280x384: 1150 against 1270).
         int th, tn;
         conv_cfg_tile(pl->cfg[i], th, tn);
-        if (ns.dtype == SV_F32 && i < L_F && th > 4 && net_get_cfg_override(ns.dtype, i) < 0)
-            pl->cfg[i] = ns.ly[i].cout <= 32 ? 2 /* th4_tn32 */ : 0 /* th4_tn64 */;
+        if (ns.dtype == SV_F32 && i < L_F && th > 4 && tn == 64 && net_get_cfg_override(ns.dtype, i) < 0)
+            pl->cfg[i] = 0 /* th4_tn64 */;
     }
     int ds;
     int cfg[NLAYERS];

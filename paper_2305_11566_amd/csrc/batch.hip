@@ -209,6 +209,9 @@ static const LayerRun kRuns[9] = {
     {L_F, BS_FPROJ, 0, 0},
 };
 
+// each layer's output level
+static const int kOutLevel[NLAYERS] = {1, 2, 3, 3, 3, 2, 1, 0, 0};
+
 static int run_cout(const NetShape &ns, int li) { return li == L_F ? 9 : ns.ly[li].cout; }
 
 // Tiles of every stage for one pair.
@@ -369,15 +372,21 @@ sv_status sv_batch_plan_create(const sv_vae_desc *desc, int max_n, int max_H, in
     pl->fin_th = gather_tile_h(ns.f, (long long)max_n * max_H * max_W);
     for (int i = 0; i < NLAYERS; ++i) {
         pl->cfg[i] = net_default_cfg(ns, i, mx, max_n);
-        // FP32 plans stay with four rows where single calls take more of 64 channels:
-        // the persistent kernels keep fewer workgroups of that tile on a CU (24 pairs of
-        // 512x256 at factor 2, layers of 64, 96 and 160 channels: 1262 against 1386 us a
-        // call; 16 of 640x384, the 1242x375 network: 593 against 628).  32 channels
-        // gain by the rows as single calls do (64 pairs to 1280x384: 1150 against 1270).
+        // FP32 plans stay with four rows where single calls take more, except for 32
+        // channels with tall tiles enough (at the largest size) for every resident
+        // workgroup to walk several: the persistent kernels keep fewer workgroups of a
+        // taller FP32 tile on a CU.  In us a call: G0 of 64 pairs to 1280x384 (15360
+        // tiles) 1199 against 1287, of 25 to 839x225 (2450) 292 against 301, of 3 to
+        // 682x320 (330) 161 against 157; G1 3840 tiles 1267 against 1287, 1161 469
+        // against 463, 480 258 against 243; layers of 64 channels, 24 pairs to 512x256,
+        // 1386 against 1262.
         int th, tn;
         conv_cfg_tile(pl->cfg[i], th, tn);
-        if (ns.dtype == SV_F32 && i < L_F && th > 4 && tn == 64 && net_get_cfg_override(ns.dtype, i) < 0)
-            pl->cfg[i] = 0 /* th4_tn64 */;
+        if (ns.dtype == SV_F32 && i < L_F && th > 4 && net_get_cfg_override(ns.dtype, i) < 0) {
+            const int k = kOutLevel[i], narrow = ns.ly[i].cout <= 32;
+            if (!narrow || (long long)max_n * conv_tiles(3 /* th8_tn32 */, mx.h[k], mx.w[k], ns.ly[i].cout) < 1536)
+                pl->cfg[i] = narrow ? 2 /* th4_tn32 */ : 0 /* th4_tn64 */;
+        }
     }
     int ds;
     int cfg[NLAYERS];

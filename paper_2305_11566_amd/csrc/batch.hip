@@ -70,12 +70,17 @@ namespace sv {
 
 // ---------------------------------------------------------------------------
 // Autotune cache: a text file, one entry per line
-//   gfx950|dt<dtype>|c<c1>,<c2>,<c3>|L<latent>|f<factor>|B<batch>|<H>x<W> <dsplit> <name0>,...,<name8>
+//   gfx950|r<revision>|dt<dtype>|c<c1>,<c2>,<c3>|L<latent>|f<factor>|B<batch>|<H>x<W> <dsplit> <name0>,...,<name8>
 // with the layers' configurations by name (sv_conv_cfg_name), loaded once per
 // process into memory; lookups take the entry of the same network and image
-// size with the nearest batch size.  A line that does not parse, or names a
-// configuration this library does not have, is ignored.
+// size with the nearest batch size, its tiles only if that is within a factor of
+// two.  A line that does not parse, or names a
+// configuration this library does not have, is ignored, and so is one timed on
+// other kernels: raise kTuneRevision when a layer's kernels, or the tile rule,
+// change.  (Revision 1 had no r field; its choices hold the layers that have row
+// kernels now to the general one.)
 // ---------------------------------------------------------------------------
+constexpr int kTuneRevision = 2;
 struct TuneEntry {
     int dt, c1, c2, c3, L, f, B, H, W, dsplit, cfg[NLAYERS];
 };
@@ -98,9 +103,10 @@ static int cfg_by_name(const std::string &name) {
 
 static bool parse_entry(const char *line, TuneEntry &t) {
     char names[400];
-    const int m = sscanf(line, "gfx950|dt%d|c%d,%d,%d|L%d|f%d|B%d|%dx%d %d %399s", &t.dt, &t.c1, &t.c2,
+    int rev;
+    const int m = sscanf(line, "gfx950|r%d|dt%d|c%d,%d,%d|L%d|f%d|B%d|%dx%d %d %399s", &rev, &t.dt, &t.c1, &t.c2,
                          &t.c3, &t.L, &t.f, &t.B, &t.H, &t.W, &t.dsplit, names);
-    if (m != 11) return false;
+    if (m != 12 || rev != kTuneRevision) return false;
     bool ok = (t.dsplit == 1 || t.dsplit == 2 || t.dsplit == 4 || t.dsplit == 8) && t.B > 0;
     std::string rest(names);
     size_t pos = 0;
@@ -116,8 +122,8 @@ static bool parse_entry(const char *line, TuneEntry &t) {
 }
 
 static void format_entry(const TuneEntry &t, char *buf, size_t n) {
-    int k = snprintf(buf, n, "gfx950|dt%d|c%d,%d,%d|L%d|f%d|B%d|%dx%d\t%d\t", t.dt, t.c1, t.c2, t.c3,
-                     t.L, t.f, t.B, t.H, t.W, t.dsplit);
+    int k = snprintf(buf, n, "gfx950|r%d|dt%d|c%d,%d,%d|L%d|f%d|B%d|%dx%d\t%d\t", kTuneRevision, t.dt, t.c1, t.c2,
+                     t.c3, t.L, t.f, t.B, t.H, t.W, t.dsplit);
     for (int i = 0; i < NLAYERS && k > 0 && (size_t)k < n; ++i)
         k += snprintf(buf + k, n - k, "%s%s", conv_cfg_name(t.cfg[i]), i + 1 < NLAYERS ? "," : "\n");
 }
@@ -137,9 +143,12 @@ static void load_cache_locked() {
     bool corrupt = false;
     while (fgets(line, sizeof line, f)) {
         TuneEntry t;
+        int rev = 1;
+        const bool other = (strncmp(line, "gfx950|dt", 9) == 0 || sscanf(line, "gfx950|r%d|", &rev) == 1) &&
+                           rev != kTuneRevision;
         if (parse_entry(line, t))
             g_tune.push_back(t);
-        else if (line[0] != '\n')
+        else if (line[0] != '\n' && !other)
             corrupt = true;
     }
     fclose(f);
@@ -166,7 +175,14 @@ bool tuned_lookup(const NetShape &ns, int B, int H, int W, int *cfg, int *dsplit
         if (d < bd) { bd = d; best = &t; }
     }
     if (!best) return false;
-    for (int i = 0; i < NLAYERS; ++i) cfg[i] = best->cfg[i];
+    // the rule's at this batch where the choice was the rule's at its own, or that batch
+    // is more than twice or less than half of this one (plans on entries of an eighth of
+    // their batch: 25 pairs to 839x225 195 us a call against 171 by the rule, 64 to
+    // 1280x384 507 against 481)
+    const Levels lv = net_levels(ns, H, W);
+    const bool like = B <= 2ll * best->B && best->B <= 2ll * B;
+    for (int i = 0; i < NLAYERS; ++i)
+        cfg[i] = !like || best->cfg[i] == net_heuristic_cfg(ns, i, lv, best->B) ? -1 : best->cfg[i];
     if (dsplit) *dsplit = best->dsplit;
     return true;
 }
@@ -388,13 +404,22 @@ sv_status sv_batch_plan_create(const sv_vae_desc *desc, int max_n, int max_H, in
                 pl->cfg[i] = narrow ? 2 /* th4_tn32 */ : 0 /* th4_tn64 */;
         }
     }
+    // The tuner times a layer as a launch with a workgroup for each tile.  A plan's
+    // launch is that while the chip holds all of its tiles at once (two workgroups a
+    // CU): those layers take the entry's tiles, the others the rule's.  (BF16, entries
+    // of the plan's batch, all layers by the entry / by the rule, us a call: 2 pairs to
+    // 1242x375 99 / 113, 8 159 / 164; 16 to 640x384 275 / 265, 64 to 1280x384 502 / 487,
+    // 128 952 / 915.)
+    constexpr long long kResident = 512;
     int ds;
     int cfg[NLAYERS];
     if (tuned_lookup(ns, max_n, max_H, max_W, cfg, &ds)) {
         pl->dsplit = cost_wta_split_override() > 0 ? cost_wta_split_override() : ds;
-        for (int i = 0; i < NLAYERS; ++i) {
-            const int ov = net_get_cfg_override(ns.dtype, i);
-            pl->cfg[i] = ov >= 0 ? ov : cfg[i];
+        for (int i = 0; i < L_F; ++i) {
+            const int k = kOutLevel[i];
+            if (cfg[i] >= 0 && net_get_cfg_override(ns.dtype, i) < 0 &&
+                (long long)max_n * conv_tiles(cfg[i], mx.h[k], mx.w[k], ns.ly[i].cout) <= kResident)
+                pl->cfg[i] = cfg[i];
         }
     }
     if (net_projects(ns, false) && g0_fits(ns.dtype, ns.c1))
@@ -703,7 +728,8 @@ sv_status sv_autotune(const sv_vae_desc *desc, int B, int H, int W, int D, int w
         const int nrep2 = B >= 16 ? 6 : 50;
         for (int pass = 0; pass < 2 && r == SV_OK; ++pass) {
             for (int i = 0; i < L_F && r == SV_OK; ++i) {
-                if (nkeep[i] < 2) continue;
+                // (a pass with the head and G3 in one kernel does not use their tiles: timed alone only)
+                if (nkeep[i] < 2 || ((i == L_HEAD || i == L_G3) && net_fuses_latent(ns))) continue;
                 float best_t = 1e30f;
                 int best_c = best_cfg[i];
                 for (int k = 0; k < nkeep[i] && r == SV_OK; ++k) {

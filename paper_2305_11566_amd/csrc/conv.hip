@@ -162,11 +162,14 @@ sv_status launch_conv_split(int dtype, int ks, int stride, int cfg, const ConvPa
         p.ksplit = 1;
     }
     if (ksplit_used) *ksplit_used = p.ksplit > 1 ? p.ksplit : 1;
-    // 5x5 layers at the default tiles
+    // the row kernel stands for the default tiles; any other is the general kernel's, so
+    // that the autotuners time what a later call with their choice runs
     const int tile = cfg % kNumTiles;
-    if ((ks == 3 || tile == kFallbackTile || tile == kTile4x32) && conv_rows_fits(dtype, ks, stride, p))
-        return launch_conv_rows(dtype, ks, stride, p, st);
-    return launch_any(dtype, ks, stride, cfg % kNumTiles, p, 0, st);
+    const bool deflt = ks == 5 ? tile == kFallbackTile || tile == kTile4x32
+                               : tile == conv_resolve_cfg(dtype, ks, stride, conv_default_tile(dtype, stride, p.Cin, p.Cout,
+                                                                                              p.B, p.Ho, p.Wo));
+    if (deflt && conv_rows_fits(dtype, ks, stride, p)) return launch_conv_rows(dtype, ks, stride, p, st);
+    return launch_any(dtype, ks, stride, tile, p, 0, st);
 }
 
 sv_status launch_split_sum(int dtype, const ConvParams &p0, int ksplit, hipStream_t st) {

@@ -34,6 +34,8 @@ struct Levels {
 Levels net_levels(const NetShape &ns, int H, int W);
 // 1 (default): an inference pass fuses the head and G3 where the widths allow
 void net_set_latent_fusion(int on);
+// Whether an inference pass runs the head and G3 as one kernel.
+bool net_fuses_latent(const NetShape &ns);
 
 // Device tensors of one forward pass.  "saved" holds what the backward needs
 // beyond the recomputed encoder; at inference it lives inside the workspace.
@@ -73,7 +75,8 @@ void net_layer_cfgs(const NetShape &ns, int B, int H, int W, int *cfg);
 // The reduction split a layer's configuration gives in a forward pass (1: none).
 int net_layer_split(const NetShape &ns, int layer, int cfg, int B, int H, int W);
 // The autotune cache entry for this network and image size with the nearest
-// batch size; false if there is none.
+// batch size; false if there is none.  cfg[i] < 0: the built-in choice for this
+// batch (nothing better was found, or the entry's batch is not a like one).
 bool tuned_lookup(const NetShape &ns, int B, int H, int W, int *cfg, int *dsplit);
 void net_set_cfg_override(int dtype, int layer, int cfg);   // -1 restores the default
 int net_get_cfg_override(int dtype, int layer);

@@ -163,7 +163,7 @@ void net_layer_cfgs(const NetShape &ns, int B, int H, int W, int *cfg) {
     const Levels lv = net_levels(ns, H, W);
     for (int i = 0; i < NLAYERS; ++i) {
         const int ov = net_get_cfg_override(ns.dtype, i);
-        cfg[i] = ov >= 0 ? ov : (have ? tuned[i] : net_default_cfg(ns, i, lv, B));
+        cfg[i] = ov >= 0 ? ov : (have && tuned[i] >= 0 ? tuned[i] : net_default_cfg(ns, i, lv, B));
         if (i < L_F) cfg[i] = conv_resolve_cfg(ns.dtype, ns.ly[i].k, ns.ly[i].stride, cfg[i]);
     }
 }
@@ -266,6 +266,7 @@ static sv_status run_split_sum(const SplitSum &ss, hipStream_t st) {
 // 1: an inference pass runs the head and G3 as one kernel where the shapes allow
 static std::atomic<int> g_latent_fusion{1};
 void net_set_latent_fusion(int on) { g_latent_fusion.store(on ? 1 : 0); }
+bool net_fuses_latent(const NetShape &ns) { return g_latent_fusion.load() && latent_fusable(ns.dtype, ns.c3, ns.L); }
 
 // with only >= 0, a forward pass launches that layer alone (the autotuner
 // times one layer at a time on buffers a full pass has filled)
@@ -353,7 +354,7 @@ sv_status net_forward(const NetShape &ns, const void *packed, const uint8_t *dis
              E2, c2, 0, 1, cfg[L_E2], part, a.part_bytes, am(AM_E1, -1, AM_E2));
     // inference: the head and G3 run as one kernel, which also finishes E3's
     // split sum when E3 runs split (E3 is then never stored)
-    const bool fuse_latent = only < 0 && !eps && !train && g_latent_fusion.load() && latent_fusable(ns.dtype, c3, L);
+    const bool fuse_latent = only < 0 && !eps && !train && net_fuses_latent(ns);
     int e3split = 1;
     if (fuse_latent) {
         ConvParams p3 = layer_params(ns, packed, L_E3, src_tensor(E2, c2, c2, 0, lv.h[2], lv.w[2], 0), none, B,

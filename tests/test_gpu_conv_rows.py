@@ -76,3 +76,35 @@ def test_3x3_rows_equal_general(dtype, f, c, H, W):
     (o1, g1), (ob, gb) = res
     assert all(np.array_equal(o1[0], o) for o in ob)
     assert np.abs(g1 - gb).max() <= 1e-5 * np.abs(g1).max()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_3x3_rows_at_the_default_tile_only(dtype):
+    """The row kernel stands for the default tiles, a set tile is the general kernel's:
+    both give the map and the gradient of a training pass of 24 images."""
+    import paper_2305_11566_amd as sv
+    B, H, W, f, c = 24, 66, 130, 2, (16, 32, 64)
+    rng = np.random.default_rng(5)
+    h, w = -(-H // f), -(-W // f)
+    disp = cuda(rng.integers(0, 48, (B, h, w)).astype(np.uint8))
+    img = cuda(rng.integers(0, 256, (B, h, w)).astype(np.uint8))
+    ref = sv.Refiner(*c, 32, f, dtype)
+    ref.pack(cuda(rng.normal(0, 0.1, ref.nparams).astype(np.float32)))
+    eps = cuda(rng.normal(0, 1, ref.latent_shape(B, H, W)).astype(np.float32))
+    dout = cuda(rng.normal(0, 1, (B, H, W)).astype(np.float32))
+    names = [sv.sv_conv_cfg_name(k) for k in range(sv.sv_num_layer_cfgs())]
+    res = []
+    try:
+        for tile in (None, "th8_tn16_k2", "th4_tn16"):
+            for layer in range(1, 8):
+                sv.sv_set_layer_cfg(layer, names.index(tile) if tile else -1)
+            saved = ref.saved_buffer(B, H, W)
+            out, _ = ref.forward(disp, img, H, W, eps=eps, saved=saved)
+            grad = ref.backward(saved, B, H, W, eps, dout, 0.0)
+            torch.cuda.synchronize()
+            res.append((out.cpu().numpy(), grad.cpu().numpy()))
+    finally:
+        for layer in range(1, 8):
+            sv.sv_set_layer_cfg(layer, -1)
+    for out, grad in res[1:]:
+        assert np.array_equal(out, res[0][0]) and np.array_equal(grad, res[0][1])

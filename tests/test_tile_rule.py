@@ -3,6 +3,9 @@ and width, never a split of the reduction (the batch plan, which does not
 split, has to equal the single calls bit for bit), and taller for larger
 grids.  Host code only: no GPU."""
 import ctypes
+import os
+import subprocess
+import sys
 
 import pytest
 
@@ -46,3 +49,34 @@ def test_large_batches_keep_within_a_grid(monkeypatch, tmp_path, dtype, c, laten
                 tn = int(n.split("_tn")[1].split("_")[0])
                 if B * -(-co // 64) <= 65535:
                     assert B * -(-co // tn) <= 65535, (n, co, B, H, W)
+
+
+def _cached(tmp_path, lines, queries):
+    """Names for (B, H, W) queries in a process of its own that reads this cache, and its messages."""
+    cache = tmp_path / "tune.tsv"
+    cache.write_text("".join(l + "\n" for l in lines))
+    code = ("import sys; sys.path.insert(0, '.')\n"
+            "from tests.test_tile_rule import _names\n"
+            f"for q in {queries!r}: print(','.join(_names((32, 64, 128), 128, 4, 'bf16', *q)))\n")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True,
+                       env=dict(os.environ, SV_AUTOTUNE_CACHE=str(cache)))
+    assert r.returncode == 0, r.stderr
+    return r.stdout.split(), r.stderr
+
+
+def test_cached_choices(tmp_path):
+    """Entries timed on other kernels are passed over without a message; a choice that
+    is the rule's at its own batch follows the rule at other batches; any other holds
+    to twice and half its batch."""
+    key = "dt1|c32,64,128|L128|f4|B%d|375x1242\t4\t%s"
+    queries = [(1, 375, 1242), (2, 375, 1242), (64, 375, 1242)]
+    rule, err = _cached(tmp_path, [], queries)
+    assert len(set(rule)) == 3
+    other = ",".join(["th8_tn16_k2"] * 9)
+    old = ["gfx950|" + key % (1, other), "gfx950|r1|" + key % (1, other)]
+    assert _cached(tmp_path, old, queries) == (rule, err)
+    assert _cached(tmp_path, ["gfx950|r2|" + key % (1, rule[0])], queries)[0] == rule
+    assert _cached(tmp_path, ["gfx950|r2|" + key % (1, other)], queries)[0] == [other, other, rule[2]]
+    out, err = _cached(tmp_path, ["garbage"], queries)
+    assert out == rule and "malformed" in err

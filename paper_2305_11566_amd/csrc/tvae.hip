@@ -1317,8 +1317,13 @@ sv_status sv_tvae_autotune(int dtype, int factor, int B, int H, int W) {
     }
     const int reps = B >= 16 ? 4 : 12;
     for (int li = 0; li < T_NL && r == SV_OK; ++li) {
-        // kernels of their own, no tile configuration
-        if (li == T_FE || li == T_YP || ((li == T_D2 || li == T_D) && g_tv_deconv_form.load() < 0)) continue;
+        // kernels of their own, no tile configuration; the default form's deconvolutions
+        // but for 16-bit ones that run split over the zero-inserted input (see
+        // tv_deconv2), which keep their split: without it they would be another kernel
+        // and other bits
+        const bool deconv = (li == T_D2 || li == T_D) && g_tv_deconv_form.load() < 0;
+        const int keep = deconv ? base[li] / conv_num_tiles() + 1 : 0;
+        if (li == T_FE || li == T_YP || (deconv && (dtype == SV_F32 || keep == 1))) continue;
         const int k = kOutLevel[li];
         const long long npix = (long long)B * lv.h[k] * lv.w[k];
         float bt = 1e30f;
@@ -1330,6 +1335,7 @@ sv_status sv_tvae_autotune(int dtype, int factor, int B, int H, int W) {
             static float dummy;
             const TvAct a = tv_act(s.es, lv, B);
             if (conv_effective_split(dtype, c, kLayers[li].cin, npix, s.n_pad[li], &dummy, a.part_bytes) != want) continue;
+            if (keep && want != keep) continue;
             cur[li] = c;
             const float t = timed(li, reps);
             if (t < bt) { bt = t; best[li] = c; }

@@ -278,3 +278,31 @@ def test_deconvolution_forms_agree():
     finally:
         sv.sv_tvae_set_deconv_form(-1)
     assert normwise(b, a) <= 1e-6
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_autotuned_16bit_pass_is_its_configurations(dtype):
+    """After tuning a small 16-bit grid, whose deconvolutions run split over the
+    zero-inserted input or in their own kernel as their configurations say, a pass
+    gives the bits of the reported configurations set one by one, and the deconvolution
+    into level 2 keeps its split."""
+    import paper_2305_11566_amd as sv
+    H, W, f, B = 61, 94, 2, 1
+    d, im = _rand_inputs(B, H, W, f, 29)
+    net = sv.TableVAE(f, dtype)
+    net.pack(cuda(flat_params(_params(31))))
+    split = sv.sv_tvae_layer_cfgs(dtype, f, B, H, W)[8].split("_s")[1:]
+    sv.sv_tvae_autotune(dtype, f, B, H, W)
+    out, _ = net.forward(cuda(d), cuda(im), H, W)
+    chosen = sv.sv_tvae_layer_cfgs(dtype, f, B, H, W)
+    names = [sv.sv_conv_cfg_name(c) for c in range(sv.sv_num_layer_cfgs())]
+    try:
+        for layer, n in enumerate(chosen):
+            sv.sv_tvae_set_layer_cfg(layer, names.index(n))
+        want, _ = net.forward(cuda(d), cuda(im), H, W)
+    finally:
+        for layer in range(len(chosen)):
+            sv.sv_tvae_set_layer_cfg(layer, -1)
+    torch.cuda.synchronize()
+    assert torch.isfinite(out).all() and torch.equal(out, want)
+    assert split and chosen[8].split("_s")[1:] == split

@@ -41,3 +41,22 @@ def test_a_gradient_that_is_not_finite_stays_where_it_is_read():
     dout[0, 11, 13] = np.inf
     b, _ = _gpu_grad(C, L, f, "f32", params, disp, img, H, W, None, dout, 0.0)
     assert not np.isfinite(b).all()
+
+
+@pytest.mark.parametrize("f,H,W", [(2, 40, 70), (4, 37, 129), (7, 30, 45)])
+def test_an_infinity_at_the_edge_stays_out_of_the_taps_that_do_not_read_it(f, H, W):
+    """dout's last column is read by the final layer's taps of the columns before and at
+    it (of three), its last row likewise: the others' weight gradients stay finite."""
+    C, L = (8, 16, 8), 8
+    disp, img, gt = _problem(H, W, f, C, L, 1, seed=8)
+    params = vae_params(C, L, seed=9)
+    for y, x, clean in ((H // 2, W - 1, np.s_[:, :, 2]), (H - 1, W // 2, np.s_[:, 2, :]),
+                        (H // 2, 0, np.s_[:, :, 0]), (0, W // 2, np.s_[:, 0, :])):
+        dout = np.random.default_rng(2).standard_normal((1, H, W))
+        dout[0, y, x] = np.inf
+        g, _ = _gpu_grad(C, L, f, "f32", params, disp, img, H, W, None, dout, 0.0)
+        dw = g[_layer_slices(C, L)[-1]][:-1].reshape(C[0] + 2, 3, 3)
+        keep = np.zeros((C[0] + 2, 3, 3), bool)
+        keep[clean] = True
+        assert np.isfinite(dw[keep]).all(), (y, x)
+        assert not np.isfinite(dw[~keep]).any(), (y, x)

@@ -75,3 +75,41 @@ def test_refiner_16bit_ragged(dtype):
         a, b = g32[sl], g16[sl]
         cos = float(a @ b / max(np.linalg.norm(a) * np.linalg.norm(b), 1e-30))
         assert cos >= 0.99, f"{name}: cosine {cos:.5f}"
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("n", [12, 64])
+def test_table_16bit_large_batches(dtype, n):
+    """12 and 64 copies of an image take the 16-bit input gradients to the row kernel
+    and the transposed convolution at two and four rows, one image alone to the general
+    kernel and to one row: the same gradient maps, so n times the gradient but for the
+    order of its FP32 sums (the FP32 bar of the backward's parity tests, per layer)."""
+    import paper_2305_11566_amd as sv
+    f, H, W = 2, 132, 260
+    r = np.random.default_rng(19)
+    d = r.integers(0, 40, (1, H // f, W // f)).astype(np.uint8)
+    im = r.integers(0, 256, (1, H // f, W // f)).astype(np.uint8)
+    dout = r.standard_normal((1, H, W)).astype(np.float32)
+    eps = r.standard_normal((1, 17, 33)).astype(np.float32)
+    net = sv.TableVAE(f, dtype)
+    net.pack(torch.randn(net.nparams, generator=torch.Generator().manual_seed(4)).mul_(0.05).cuda())
+    names = [sv.sv_conv_cfg_name(c) for c in range(sv.sv_num_layer_cfgs())]
+    res = []
+    try:
+        for layer in range(sv.sv_tvae_num_layers()):  # no split reductions: the same maps at both sizes
+            sv.sv_tvae_set_layer_cfg(layer, names.index("th4_tn16"))
+        for k in (1, n):
+            dd, ii, do, ee = (cuda(np.repeat(a, k, axis=0)) for a in (d, im, dout, eps))
+            out, _ = net.forward(dd, ii, H, W, eps=ee)
+            g = net.backward(dd, ii, H, W, do, eps=ee)
+            res.append((out.cpu().numpy(), g.cpu().numpy().astype(np.float64)))
+    finally:
+        for layer in range(sv.sv_tvae_num_layers()):
+            sv.sv_tvae_set_layer_cfg(layer, -1)
+    assert (res[1][0] == res[0][0]).all()
+    at = 0
+    for o, c, k in [(32, 1, 5), (32, 1, 5), (16, 64, 5), (8, 16, 5), (32, 24, 5), (16, 32, 5), (2, 48, 1), (32, 1, 1),
+                    (16, 80, 5), (16, 96, 5), (8, 40, 5), (16, 48, 5), (1, 81, 5)]:
+        sl = slice(at, at + o * c * k * k + o)
+        assert normwise(res[1][1][sl], n * res[0][1][sl]) <= 1e-4, (at, o, c, k)
+        at = sl.stop

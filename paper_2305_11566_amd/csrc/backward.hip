@@ -436,7 +436,7 @@ static sv_status dgrad(const NetShape &ns, const void *packed, int li, ConvSrc d
     const int ks = ns.ly[li].k;
     if (dy.kind == SRC_ZINS && tconv_fits(ns.dtype, ks, p)) return launch_tconv(ns.dtype, ks, p, st);
     const int cfg = ks == 3 ? conv_default_tile(ns.dtype, 1, dy.C, cout_needed, B, Hi, Wi)
-                            : (cout_needed <= 16 ? 5 : (cout_needed <= 32 ? 2 : 0));
+                            : (cout_needed <= 16 ? T4_16 : (cout_needed <= 32 ? T4_32 : T4_64));
     return launch_conv(ns.dtype, ks, 1, cfg, p, st);
 }
 

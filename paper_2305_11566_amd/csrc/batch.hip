@@ -400,8 +400,8 @@ sv_status sv_batch_plan_create(const sv_vae_desc *desc, int max_n, int max_H, in
         conv_cfg_tile(pl->cfg[i], th, tn);
         if (ns.dtype == SV_F32 && i < L_F && th > 4 && net_get_cfg_override(ns.dtype, i) < 0) {
             const int k = kOutLevel[i], narrow = ns.ly[i].cout <= 32;
-            if (!narrow || (long long)max_n * conv_tiles(3 /* th8_tn32 */, mx.h[k], mx.w[k], ns.ly[i].cout) < 1536)
-                pl->cfg[i] = narrow ? 2 /* th4_tn32 */ : 0 /* th4_tn64 */;
+            if (!narrow || (long long)max_n * conv_tiles(T8_32, mx.h[k], mx.w[k], ns.ly[i].cout) < 1536)
+                pl->cfg[i] = narrow ? T4_32 : T4_64;
         }
     }
     // The tuner times a layer as a launch with a workgroup for each tile.  A plan's

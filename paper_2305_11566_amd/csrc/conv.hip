@@ -37,16 +37,22 @@ namespace sv {
 // id = tile + kNumTiles * (ksplit - 1), ksplit = 1 .. kMaxSplit.  A split only
 // applies to uniform launches that bring a partial-sum buffer.
 struct CfgDesc { int TH, TN, WM, KCM; const char *name; };
-static const CfgDesc kCfgs[] = {
+static constexpr CfgDesc kCfgs[] = {
 #define SV_CFG(i, TH, TN, WM, KCM, name) {TH, TN, WM, KCM, name},
     SV_CONV_CFGS(SV_CFG)
 #undef SV_CFG
 };
 static constexpr int kNumTiles = (int)(sizeof(kCfgs) / sizeof(kCfgs[0]));
 static constexpr int kMaxSplit = CONV_MAX_SPLIT;
-static constexpr int kFallbackTile = 5;  // th4_tn16
-static constexpr int kTile4x32 = 2;      // th4_tn32
-static constexpr int kTile4x64 = 0;      // th4_tn64
+static constexpr bool is_tile(int t, int th, int tn, int kcm) {
+    return kCfgs[t].TH == th && kCfgs[t].TN == tn && kCfgs[t].KCM == kcm;
+}
+static_assert(is_tile(T4_64, 4, 64, 1) && is_tile(T8_64, 8, 64, 1) && is_tile(T4_32, 4, 32, 1) &&
+                  is_tile(T8_32, 8, 32, 1) && is_tile(T2_64, 2, 64, 1) && is_tile(T4_16, 4, 16, 1) &&
+                  is_tile(T4_16_K4, 4, 16, 4) && is_tile(T4_32_K2, 4, 32, 2) && is_tile(T4_16_K2, 4, 16, 2) &&
+                  is_tile(T2_32_K2, 2, 32, 2) && is_tile(T16_32, 16, 32, 1),
+              "ConvTileId names the table's rows");
+static constexpr int kFallbackTile = T4_16;
 int conv_num_tiles() { return kNumTiles; }
 int conv_num_cfgs() { return kNumTiles * kMaxSplit; }
 
@@ -165,7 +171,7 @@ sv_status launch_conv_split(int dtype, int ks, int stride, int cfg, const ConvPa
     // the row kernel stands for the default tiles; any other is the general kernel's, so
     // that the autotuners time what a later call with their choice runs
     const int tile = cfg % kNumTiles;
-    const bool deflt = ks == 5 ? tile == kFallbackTile || tile == kTile4x32
+    const bool deflt = ks == 5 ? tile == T4_16 || tile == T4_32
                                : tile == conv_resolve_cfg(dtype, ks, stride, conv_default_tile(dtype, stride, p.Cin, p.Cout,
                                                                                               p.B, p.Ho, p.Wo));
     if (deflt && conv_rows_fits(dtype, ks, stride, p)) return launch_conv_rows(dtype, ks, stride, p, st);
@@ -230,8 +236,6 @@ int conv_persistent_cfg(int cfg) {
 // accumulators and staging registers allow two workgroups a CU there (G2 at
 // batch 64 101 against 118 us, E2 50 against 62).
 static int rule_tile(int dtype, int stride, int cin, int cout, int B, int Ho, int Wo) {
-    enum { T4_64 = 0, T8_64 = 1, T4_32 = 2, T8_32 = 3, T2_64 = 4, T4_16 = 5, T4_16_K4 = 6, T4_32_K2 = 7, T4_16_K2 = 8,
-           T2_32_K2 = 11, T16_32 = 16 };
     constexpr long long kEnough = 400;
     auto wgs = [&](int th, int tn) { return (long long)B * cdiv(Ho, th) * cdiv(Wo, 16) * cdiv(cout, tn); };
     const bool f32 = dtype == SV_F32, i8 = dtype == SV_I8;
@@ -260,7 +264,7 @@ static int rule_tile(int dtype, int stride, int cin, int cout, int B, int Ho, in
 int conv_default_tile(int dtype, int stride, int cin, int cout, int B, int Ho, int Wo) {
     const int t = rule_tile(dtype, stride, cin, cout, B, Ho, Wo);
     if ((long long)B * cdiv(cout, kCfgs[t].TN) <= CONV_MAX_PLANES) return t;
-    return cout <= 16 ? kFallbackTile : (cout <= 32 ? kTile4x32 : kTile4x64);
+    return cout <= 16 ? T4_16 : (cout <= 32 ? T4_32 : T4_64);
 }
 
 bool conv_cfg_projects(int cfg, int cout) {

@@ -165,6 +165,12 @@ void conv_cfg_tile(int cfg, int &TH, int &TN);
 // cfg, or the fallback tile shape (same split) when cfg's tile does not fit
 // the LDS for this kernel size and stride; launches resolve the same way
 int conv_resolve_cfg(int dtype, int ks, int stride, int cfg);
+// The tile shapes that the built-in choices name (rows x channels, base chunks staged
+// at once): indices of the table in conv_impl.h, checked in conv.hip.
+enum ConvTileId {
+    T4_64 = 0, T8_64 = 1, T4_32 = 2, T8_32 = 3, T2_64 = 4, T4_16 = 5, T4_16_K4 = 6, T4_32_K2 = 7, T4_16_K2 = 8,
+    T2_32_K2 = 11, T16_32 = 16
+};
 int conv_num_tiles();  // tile shapes; cfg = tile + conv_num_tiles() * (ksplit - 1)
 constexpr int CONV_MAX_SPLIT = 4;
 // images x channel tiles x split of a uniform launch

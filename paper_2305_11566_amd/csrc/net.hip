@@ -136,9 +136,7 @@ int net_heuristic_cfg(const NetShape &ns, int layer, const Levels &lv, int B) {
         const int k = out_level[layer];
         return conv_default_tile(ns.dtype, ns.ly[layer].stride, ns.ly[layer].cin, cout, B, lv.h[k], lv.w[k]);
     }
-    if (cout <= 16) return 5;   // th4_tn16
-    if (cout <= 32) return 2;   // th4_tn32
-    return 0;                   // th4_tn64
+    return cout <= 16 ? T4_16 : (cout <= 32 ? T4_32 : T4_64);
 }
 
 bool net_projects(const NetShape &ns, bool train) {
@@ -147,7 +145,7 @@ bool net_projects(const NetShape &ns, bool train) {
 
 int net_g0_proj_cfg(const NetShape &ns, int cfg) {
     int c = conv_resolve_cfg(ns.dtype, 3, 1, cfg % conv_num_tiles());  // no split
-    if (!conv_cfg_projects(c, ns.c1)) c = ns.c1 <= 32 ? 2 /* th4_tn32 */ : 0 /* th4_tn64 */;
+    if (!conv_cfg_projects(c, ns.c1)) c = ns.c1 <= 32 ? T4_32 : T4_64;
     return c;
 }
 

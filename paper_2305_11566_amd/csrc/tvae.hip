@@ -182,13 +182,13 @@ std::map<std::tuple<int, int, int, int, int>, std::array<int, T_NL>> g_tv_tuned;
 // up to four channel ranges so that more CUs take part.
 int tv_heuristic_cfg(int layer, int B, int Ho, int Wo) {
     const int tn = kLayers[layer].cout <= 16 ? 16 : 32;
-    const int tile = tn == 16 ? 5 /* th4_tn16 */ : 2 /* th4_tn32 */;
+    const int tile = tn == 16 ? T4_16 : T4_32;
     const long long nwg = (long long)cdiv(Wo, 16) * cdiv(Ho, 4) * B * cdiv(kLayers[layer].cout, tn);
     int split = 1;
     while (split < CONV_MAX_SPLIT && nwg * split < 256) ++split;
     if (layer == T_EN2) {
-        if (nwg < 256) return 5 /* th4_tn16 */ + conv_num_tiles() * (split - 1);
-        if ((long long)cdiv(Wo, 16) * cdiv(Ho, 8) * B >= 200) return 3 /* th8_tn32 */;
+        if (nwg < 256) return T4_16 + conv_num_tiles() * (split - 1);
+        if ((long long)cdiv(Wo, 16) * cdiv(Ho, 8) * B >= 200) return T8_32;
     }
     return tile + conv_num_tiles() * (split - 1);
 }
@@ -955,7 +955,7 @@ sv_status tv_dgrad(const TvShape &s, const void *packed, int li, ConvSrc dy, int
     p.mask = mask_hi ? (const char *)act + (size_t)out_coff * s.es : nullptr;
     p.mask_pitch = out_pitch; p.mask_lo = mask_lo; p.mask_hi = mask_hi;
     if (dy.kind == SRC_ZINS && tconv_fits(s.dtype, kLayers[li].k, p)) return launch_tconv(s.dtype, kLayers[li].k, p, st);
-    const int cfg = p.Cout <= 16 ? 5 : 2;
+    const int cfg = p.Cout <= 16 ? T4_16 : T4_32;
     return launch_conv(s.dtype, kLayers[li].k, stride, cfg, p, st);
 }
 

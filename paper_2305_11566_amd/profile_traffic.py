@@ -143,7 +143,7 @@ def summarize(fetch_dir: str, write_dir: str, names_json: str, out_json: str) ->
         elif "k_conv_split_reduce" in n:
             cur[-1][1] += fb
             cur[-1][2] += wb
-        elif "k_conv<" in n or "k_latent<" in n or "k_enc1<" in n:
+        elif "k_conv<" in n or "k_conv_rows<" in n or "k_latent<" in n or "k_enc1<" in n:
             cur.append([n, fb, wb])
         elif "k_final" in n:
             forwards.append((cur, (fb, wb)))
@@ -159,7 +159,7 @@ def summarize(fetch_dir: str, write_dir: str, names_json: str, out_json: str) ->
         assert len(convs) == len(layers)
         for layer, (n, fb, wb), cfg in zip(layers, convs, cfgs):
             entries[f"f32|B1|{H}x{W}|{layer}|{cfg}"] = {"fetch_bytes": round(fb), "write_bytes": round(wb),
-                                                        "kernel": n.split("(")[0]}
+                                                        "kernel": n.replace("(anonymous namespace)::", "").split("(")[0]}
         final = {"fetch_bytes": round(fin[0]), "write_bytes": round(fin[1])}
     doc = {"source_hash": source_hash(), "counter_scale": {"FETCH_SIZE": s_fetch, "WRITE_SIZE": s_write},
            "census": census, "cost_wta": cost, "final_gather": final, "layers": entries}

@@ -70,6 +70,19 @@ def test_traffic_summary_fused_and_split(tmp_path):
     assert doc["source_hash"] == pt.source_hash()
 
 
+def test_traffic_summary_takes_the_row_kernel_for_a_layer(tmp_path):
+    """A layer at its default tile may run as the row kernel (in a namespace of its own)."""
+    rows = [(n.replace("sv::k_conv<0, 3, 2, 2, 32, 2, 2>", "sv::(anonymous namespace)::k_conv_rows<0, 3, 2, 1, 2, 0>")
+             if v == 12.0 else n, v) for n, v in _dispatches()]
+    for d in ("tf", "tw"):
+        _write_counters(tmp_path / d, rows)
+    (tmp_path / "names.json").write_text(json.dumps([["c%d" % i for i in range(9)], ["d%d" % i for i in range(9)]]))
+    pt.summarize(str(tmp_path / "tf"), str(tmp_path / "tw"), str(tmp_path / "names.json"), str(tmp_path / "o.json"))
+    layers = json.loads((tmp_path / "o.json").read_text())["layers"]
+    assert "k_conv_rows" in layers["f32|B1|375x1242|E2|d1"]["kernel"]
+    assert layers["f32|B1|375x1242|G2|d5"]["write_bytes"] > 0
+
+
 def test_bench_merges_fused_latent_stage():
     prof = {"E3": (1.0, 5), "HEAD": (2.0, 5), "G3": (0.0, 0), "G2": (3.0, 5)}
     m = bench.merge_latent(prof)

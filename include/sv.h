@@ -376,8 +376,11 @@ typedef struct sv_batch_plan sv_batch_plan;
  * ranges up to max_D through the whole path (census, cost + WTA, network)
  * with one launch per stage over all pairs, captured as one hipGraph and
  * replayed per call.  The plan owns its device buffers and graph.
- * win_w, win_h: census window.  Tile shapes come from the autotune cache when
- * it has an entry for these sizes (see sv_autotune), else from defaults.
+ * win_w, win_h: census window.  Tile shapes are the built-in choice for max_n
+ * pairs of the largest size; layers small enough there that every tile has a
+ * resident workgroup take those of an autotune cache entry for that size and a
+ * batch between half and twice max_n (see sv_autotune).  Results do not depend
+ * on them.
  */
 sv_status sv_batch_plan_create(const sv_vae_desc *desc, int max_n, int max_H, int max_W,
                                int max_D, int win_w, int win_h, sv_batch_plan **plan);
@@ -429,9 +432,12 @@ sv_status sv_paper_batch(const sv_paper_desc *desc, const sv_pair *pairs, int n,
  * Time the candidate configurations of every stage for this desc and shape
  * on the current device and store the fastest in the autotune cache (a text
  * file at $SV_AUTOTUNE_CACHE, default ~/.cache/sv_autotune.tsv, one line per
- * gfx arch, dtype, channels, latent, factor, batch and size).  A missing or
- * corrupt cache falls back to defaults.  Allocates and frees its own scratch
- * buffers; synchronises.
+ * gfx arch, revision of the kernels, dtype, channels, latent, factor, batch and
+ * size).  Later calls on this size and a batch between half and twice this one
+ * (the nearest entry's) use them; where the fastest is the built-in choice,
+ * they use the built-in choice for their own batch.  A missing or corrupt
+ * cache, and lines of another revision, fall back to defaults.  Allocates and
+ * frees its own scratch buffers; synchronises.
  */
 sv_status sv_autotune(const sv_vae_desc *desc, int B, int H, int W, int D, int win_w, int win_h);
 
@@ -443,7 +449,11 @@ sv_status sv_autotune(const sv_vae_desc *desc, int B, int H, int W, int D, int w
  * tile shape.  A split > 1 adds the parts' FP32 partial sums in a fixed
  * order, so results are deterministic per split but differ from the
  * unsplit ones by rounding.  Splits apply to sv_vae_forward only (capped by
- * its workspace); the batch plan and the backward pass run unsplit. */
+ * its workspace); the batch plan and the backward pass run unsplit.  Layer 0
+ * (E1) has no configuration; layer 7 (G0) at inference in 16-bit types and
+ * INT8 with up to 32 channels takes the tile's rows alone, and layers 3 and 4
+ * none when they run as one kernel (sv_set_latent_fusion).  The built-in
+ * choice of a 3x3 layer may run as another kernel with the same results. */
 sv_status sv_set_layer_cfg(int layer, int cfg);
 int sv_num_layer_cfgs(void);
 
@@ -485,8 +495,8 @@ sv_status sv_profile_read(float *ms_sum, int *counts);
 
 /* The tile configuration (an index, see sv_conv_cfg_name) each of the 9
  * network layers uses for a forward pass of batch B at H x W: an explicit
- * sv_set_layer_cfg override, else the autotune cache entry for this shape,
- * else the default.  cfg_out: (host) int[9]. */
+ * sv_set_layer_cfg override, else the autotune cache entry for this size (see
+ * sv_autotune), else the default.  cfg_out: (host) int[9]. */
 sv_status sv_layer_cfgs(const sv_vae_desc *desc, int B, int H, int W, int *cfg_out);
 const char *sv_conv_cfg_name(int cfg);
 
@@ -597,19 +607,24 @@ sv_status sv_tvae_backward(int dtype, int factor, const void *packed_w, const ui
 /* Tile configuration of launched layer `layer` (0 .. sv_tvae_num_layers()-1:
  * FE, EN_1, EN_1_R, EN_2, EN_2_R, mu&sigma, D_1, D_1_R, D_2, D_2_R, D, Y's tap
  * projection) of sv_tvae_forward, as sv_set_layer_cfg; -1 restores the
- * default.  Results do not depend on the tile shape.  Errors: SV_ERR_RANGE. */
+ * default.  Results do not depend on the tile shape.  FE and Y run as kernels
+ * of their own without a tile: theirs is accepted and unused, and so is that
+ * of D_2 and D in the default form unless they are 16-bit and it splits the
+ * reduction (sv_tvae_set_deconv_form).  Errors: SV_ERR_RANGE. */
 sv_status sv_tvae_set_layer_cfg(int layer, int cfg);
 int sv_tvae_num_layers(void);
 
 /* Form of the two stride-2 deconvolutions (D_2, D) in sv_tvae_forward: -1
  * (default) the transposed convolution's own kernel (16-bit layers whose
- * configuration splits the reduction: form 0); 0 one 5x5 convolution over
+ * configuration splits the reduction, and maps of 2^31 elements an image:
+ * form 0); 0 one 5x5 convolution over
  * the zero-inserted input (the same bits where its reduction is not split); 1
  * four polyphase 3x3 launches (one per output parity class, over the un-inserted
  * input; another FP32 summation order).  Errors: SV_ERR_RANGE. */
 sv_status sv_tvae_set_deconv_form(int form);
 
-/* Times every tile configuration of each launched layer of sv_tvae_forward
+/* Times every configuration of each launched layer of sv_tvae_forward that
+ * has one (see sv_tvae_set_layer_cfg; 16-bit D_2 and D at their split)
  * alone for this shape (zero weights and inputs; timing does not depend on
  * values), keeps the fastest per layer if the whole pass then runs faster
  * than with the defaults, and uses them for later calls with exactly this
@@ -618,7 +633,8 @@ sv_status sv_tvae_set_deconv_form(int form);
  * the tile shape (a split changes the FP32 summation order only).
  * Errors: SV_ERR_DTYPE, SV_ERR_RANGE, SV_ERR_SHAPE, SV_ERR_HIP. */
 sv_status sv_tvae_autotune(int dtype, int factor, int B, int H, int W);
-/* The configuration each launched layer uses for this shape (host int [12]). */
+/* The configuration each launched layer uses for this shape (host int [12]);
+ * the built-in one for layers that run without. */
 sv_status sv_tvae_layer_cfgs(int dtype, int factor, int B, int H, int W, int *cfg_out);
 
 #ifdef __cplusplus

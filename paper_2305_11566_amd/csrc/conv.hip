@@ -22,8 +22,8 @@
 // the reduction is fixed by the base chunk and the step, not by the tile
 // shape, so every tile shape gives bitwise-identical results.  The kernel
 // templates live in conv_impl.h and are instantiated per compute dtype in
-// conv_f32.hip / conv_bf16.hip / conv_f16.hip; this file holds the tile
-// table, the dispatch and the weight packing.
+// conv_f32.hip / conv_bf16.hip / conv_f16.hip / conv_i8.hip; this file holds the
+// tile table, the dispatch and the INT8 weight packing (pack.hip the others').
 #include <algorithm>
 #include <cstdio>
 #include <mutex>

@@ -321,8 +321,9 @@ sv_status launch_g0(int dtype, int th, const ConvParams &p, int grid, hipStream_
 bool tconv_fits(int dtype, int ks, const ConvParams &p);
 sv_status launch_tconv(int dtype, int ks, const ConvParams &p, hipStream_t s);
 // An unsplit 3x3 or 5x5 convolution of one map read in place, or a 3x3 one of
-// [resize(map) | second source] (conv_rows.hip): weights, epilogue and bits as launch_conv.  conv_rows_fits:
-// the launches it takes.
+// [resize(map) | second source] (conv_rows.hip): weights, epilogue and bits as the general kernel.  conv_rows_fits:
+// the launches it takes; launch_conv runs it where the configuration is the default
+// tile, unsplit.
 bool conv_rows_fits(int dtype, int ks, int stride, const ConvParams &p);
 sv_status launch_conv_rows(int dtype, int ks, int stride, const ConvParams &p, hipStream_t s);
 // the tile shape for a 3x3 layer of this size that nothing was tuned for

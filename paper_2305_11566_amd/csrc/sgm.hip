@@ -138,7 +138,7 @@ k_sgm_paths(const uint8_t *__restrict__ cost, int B, int h, int w, int D, int Dp
     const int d0 = lane * DPL;
     const long long step = ((long long)dy * w + dx) * Dp, at0 = ((long long)y0 * w + x0) * Dp;
     // per word: where it is read and written; a word past Dp reads the first
-    // costs of the image and writes this lane's slot of the sink
+    // costs of the image and writes the workgroup's word of the sink
     const uint8_t *lp[NWD];
     uint8_t *sp[NWD];
     long long st[NWD];
@@ -310,7 +310,7 @@ k_sgm_wta(const uint8_t *__restrict__ vol, size_t nvox, int D, int Dp, int nch, 
 // in LDS (use_last = 0), are searched.
 // (94 rows of 311 pixels, D = 48: 5 us; 29 us with one wave a row and the search.)
 constexpr int SMP_MAXW = 16384;
-constexpr int SMP_LASTW = 8192;  // widest row with the table: 41 KB of LDS
+constexpr int SMP_LASTW = 8192;  // widest row with the table: 43 KB of LDS
 __global__ void __launch_bounds__(256)
 k_smp(const uint8_t *__restrict__ disp, int w, int D, int use_last, uint8_t *__restrict__ out)
 {

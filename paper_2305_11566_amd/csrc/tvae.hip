@@ -498,8 +498,9 @@ ConvSrc tsrc(const void *p, int C, int pitch, int coff, int hs, int ws, int kind
     return s;
 }
 
-// Form of the stride-2 deconvolutions: -1 their own kernel (k_tconv), 0 the
-// general convolution over the zero-inserted grid, 1 as four polyphase ones (a
+// Form of the stride-2 deconvolutions: -1 their own kernel (k_tconv; tv_deconv2 has
+// the exceptions), 0 the general convolution over the zero-inserted grid, 1 as four
+// polyphase ones (a
 // pass of 16 BF16 images of 1242x375 261 us by the first against 341 by the
 // faster of the others for each layer, of one in FP32 136 against 148).
 std::atomic<int> g_tv_deconv_form{-1};

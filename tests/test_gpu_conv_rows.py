@@ -1,5 +1,6 @@
-"""The kernel of the 5x5 layers that read one map in place against the general
-convolution (taken at another tile shape): the same bits."""
+"""The row kernel (5x5 and 3x3 layers that read one map in place, 3x3 ones of a
+resized map) against the general convolution, taken at another tile shape or a
+smaller batch: the same bits."""
 import numpy as np
 import pytest
 import torch

@@ -105,18 +105,21 @@ __device__ __forceinline__ void conv_bias4(const ConvParams &p, int nbase, float
 }
 
 // Returns max |stored value| over the channels it wrote (for amax_out).
-template <int DT0>
+// VEC: the backward terms of the four channels by one load each where they lie
+// aligned, for the row and transposed convolutions.  In the general kernel that, or a
+// test of the mask's window for each channel, costs every layer three to four registers
+// and some a wave a SIMD (FP32 G0 of the 256x128 network, 28 maps 206x328, 264 us
+// against 228): there one test stands for the four channels.
+template <int DT0, bool VEC = false>
 __device__ __forceinline__ float conv_epilogue(const ConvParams &p, size_t pix, int nbase,
                                                const float (&acc)[4], const float (&bias)[4]) {
     constexpr int DT = Store<DT0>::v;
     using T = typename Elem<DT>::T;
     float r[4];
     const bool full = nbase + 4 <= p.Cout;
-    // the backward terms of the four channels (INT8 has none), by one load each where
-    // they lie aligned
-    constexpr bool BWD = DT0 != SV_I8;
+    constexpr bool BWD = DT0 != SV_I8;  // (INT8 has no backward terms)
     float add[4] = {0.f, 0.f, 0.f, 0.f}, mv[4] = {1.f, 1.f, 1.f, 1.f};
-    if (BWD && p.add) {
+    if (VEC && BWD && p.add) {
         const float *q = p.add + (pix * p.add_pitch + p.add_coff + nbase);
         if (full && (uintptr_t)q % 16 == 0) {
             const f32x4 v = *(const f32x4 *)q;
@@ -128,7 +131,7 @@ __device__ __forceinline__ float conv_epilogue(const ConvParams &p, size_t pix, 
                 if (nbase + i < p.Cout) add[i] = q[i];
         }
     }
-    if (BWD && p.mask && nbase + 4 > p.mask_lo && nbase < p.mask_hi) {
+    if (VEC && BWD && p.mask && nbase + 4 > p.mask_lo && nbase < p.mask_hi) {
         typedef T T4 __attribute__((ext_vector_type(4)));
         const T *q = (const T *)p.mask + (pix * p.mask_pitch + nbase);
         if (nbase >= p.mask_lo && nbase + 4 <= p.mask_hi && (uintptr_t)q % sizeof(T4) == 0) {
@@ -143,10 +146,17 @@ __device__ __forceinline__ float conv_epilogue(const ConvParams &p, size_t pix, 
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
+        const int n = nbase + i;
         float val = acc[i] + bias[i];
         if (p.act) val = val > 0.f ? val : 0.1f * val;
-        if (BWD && p.add) val += add[i];
-        if (BWD && p.mask) val *= mv[i] > 0.f ? 1.0f : 0.1f;
+        if (VEC) {
+            if (BWD && p.add) val += add[i];
+            if (BWD && p.mask) val *= mv[i] > 0.f ? 1.0f : 0.1f;
+        } else if (BWD && n < p.Cout) {
+            if (p.add) val += p.add[pix * p.add_pitch + p.add_coff + n];
+            if (p.mask && nbase >= p.mask_lo && nbase < p.mask_hi)
+                val *= Elem<DT>::load((const T *)p.mask + pix * p.mask_pitch + n) > 0.f ? 1.0f : 0.1f;
+        }
         r[i] = val;
     }
     const size_t o = pix * p.out_pitch + p.out_coff + nbase;

@@ -103,7 +103,7 @@ struct ConvParams {
     const float *add;    // += add[pix * add_pitch + add_coff + n] (FP32)
     int add_pitch, add_coff;
     const void *mask;    // *= (mask[pix * mask_pitch + n] > 0 ? 1 : 0.1), compute dtype,
-    int mask_pitch;      // for channels mask_lo <= n < mask_hi <= Cout
+    int mask_pitch;      // for channels mask_lo <= n < mask_hi <= Cout, multiples of four
     int mask_lo, mask_hi;
     // pair-table mode (persistent over the tiles of all pairs); NULL = uniform batch
     const PairTable *tab;

@@ -105,12 +105,13 @@ __device__ __forceinline__ void conv_bias4(const ConvParams &p, int nbase, float
 }
 
 // Returns max |stored value| over the channels it wrote (for amax_out).
-// VEC: the backward terms of the four channels by one load each where they lie
-// aligned, for the row and transposed convolutions.  In the general kernel that, or a
-// test of the mask's window for each channel, costs every layer three to four registers
-// and some a wave a SIMD (FP32 G0 of the 256x128 network, 28 maps 206x328, 264 us
-// against 228): there one test stands for the four channels.
-template <int DT0, bool VEC = false>
+// The backward terms of the four channels by one load each where they lie aligned,
+// behind one test that a forward launch skips: with a test a channel a forward pass
+// took 1 to 2 % longer (table network, 1242x375 FP32: 135.6 us against 131.7); loaded
+// ahead of the sums, or with a test of the mask's window for each channel, they cost
+// every general kernel three to four registers and some a wave a SIMD (FP32 G0 of the
+// 256x128 network, 28 maps 206x328: 264 us against 228).
+template <int DT0>
 __device__ __forceinline__ float conv_epilogue(const ConvParams &p, size_t pix, int nbase,
                                                const float (&acc)[4], const float (&bias)[4]) {
     constexpr int DT = Store<DT0>::v;
@@ -118,46 +119,39 @@ __device__ __forceinline__ float conv_epilogue(const ConvParams &p, size_t pix, 
     float r[4];
     const bool full = nbase + 4 <= p.Cout;
     constexpr bool BWD = DT0 != SV_I8;  // (INT8 has no backward terms)
-    float add[4] = {0.f, 0.f, 0.f, 0.f}, mv[4] = {1.f, 1.f, 1.f, 1.f};
-    if (VEC && BWD && p.add) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float val = acc[i] + bias[i];
+        if (p.act) val = val > 0.f ? val : 0.1f * val;
+        r[i] = val;
+    }
+    if (BWD && p.add) {
         const float *q = p.add + (pix * p.add_pitch + p.add_coff + nbase);
         if (full && (uintptr_t)q % 16 == 0) {
             const f32x4 v = *(const f32x4 *)q;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) add[i] = v[i];
+            for (int i = 0; i < 4; ++i) r[i] += v[i];
         } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                if (nbase + i < p.Cout) add[i] = q[i];
+                if (nbase + i < p.Cout) r[i] += q[i];
         }
     }
-    if (VEC && BWD && p.mask && nbase + 4 > p.mask_lo && nbase < p.mask_hi) {
+    if (BWD && p.mask && nbase >= p.mask_lo && nbase < p.mask_hi) {
         typedef T T4 __attribute__((ext_vector_type(4)));
         const T *q = (const T *)p.mask + (pix * p.mask_pitch + nbase);
-        if (nbase >= p.mask_lo && nbase + 4 <= p.mask_hi && (uintptr_t)q % sizeof(T4) == 0) {
+        if (full && (uintptr_t)q % sizeof(T4) == 0) {
             const T4 v = *(const T4 *)q;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) mv[i] = Elem<DT>::load((const T *)&v + i);
+            for (int i = 0; i < 4; ++i) {
+                const T e = v[i];
+                r[i] *= Elem<DT>::load(&e) > 0.f ? 1.0f : 0.1f;
+            }
         } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                if (nbase + i >= p.mask_lo && nbase + i < p.mask_hi) mv[i] = Elem<DT>::load(q + i);
+                if (nbase + i < p.Cout) r[i] *= Elem<DT>::load(q + i) > 0.f ? 1.0f : 0.1f;
         }
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int n = nbase + i;
-        float val = acc[i] + bias[i];
-        if (p.act) val = val > 0.f ? val : 0.1f * val;
-        if (VEC) {
-            if (BWD && p.add) val += add[i];
-            if (BWD && p.mask) val *= mv[i] > 0.f ? 1.0f : 0.1f;
-        } else if (BWD && n < p.Cout) {
-            if (p.add) val += p.add[pix * p.add_pitch + p.add_coff + n];
-            if (p.mask && nbase >= p.mask_lo && nbase < p.mask_hi)
-                val *= Elem<DT>::load((const T *)p.mask + pix * p.mask_pitch + n) > 0.f ? 1.0f : 0.1f;
-        }
-        r[i] = val;
     }
     const size_t o = pix * p.out_pitch + p.out_coff + nbase;
     float amax = 0.f;

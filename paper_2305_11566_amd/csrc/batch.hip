@@ -423,7 +423,7 @@ sv_status sv_batch_plan_create(const sv_vae_desc *desc, int max_n, int max_H, in
         }
     }
     if (net_projects(ns, false) && g0_fits(ns.dtype, ns.c1))
-        pl->g0_th = g0_tile_h(pl->cfg[L_G0] % conv_num_tiles());
+        pl->g0_th = net_g0_rows(ns, pl->cfg[L_G0], mx, max_n);
     for (int i = 0; i < L_F; ++i)
         pl->cfg[i] = conv_resolve_cfg(ns.dtype, ns.ly[i].k, ns.ly[i].stride, conv_persistent_cfg(pl->cfg[i]));
     if (net_projects(ns, false)) pl->cfg[L_G0] = net_g0_proj_cfg(ns, pl->cfg[L_G0]);

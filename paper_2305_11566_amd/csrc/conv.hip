@@ -225,38 +225,69 @@ int conv_persistent_cfg(int cfg) {
 // tile does not change results, so this is a matter of speed alone).
 //
 // A taller or wider tile spends less on staging its halo, its pixel table and
-// the weights, until the chip is left with idle CUs.  The line is kEnough = 400
-// workgroups (1.5 a CU): in every measured pair of neighbouring shapes the
-// larger tile won with 480 workgroups and lost with 240 (BF16 G0 of the
-// 1242x375 network: batch 4 16-row 14.4 / 8-row 19.0 / 4-row 22.7 us, batch 2
-// 12.6 / 10.6 / 14.3; G1: batch 8 18.3 / 14.2 / 18.9).  Below it the smallest
-// tiles; 16-channel layers take 16 rows (in 32-channel tiles) in 16-bit types
-// (64 pairs of 256x128, G0: 49 against 59 us) but not in FP32 (81 against 66),
-// where half the products would be padding.  INT8 keeps to 32 channels, its
-// accumulators and staging registers allow two workgroups a CU there (G2 at
-// batch 64 101 against 118 us, E2 50 against 62).
+// the weights, until the chip is left with idle CUs: two workgroups a CU are
+// resident, so the lines lie between one workgroup a CU (256) and somewhat past
+// the first full wave (512, 700).  They are fitted to 5900 timings of every tile
+// at 4 to 74112 output pixels a map, 1 to 64 maps, 8 to 256 channels and each
+// type, and are within 2.2 % of the best tile on average (the one tile per width
+// that stood here first, four rows of 16, 32 or 64 channels: 34 %).  By group,
+// this rule against those tiles:
+//   16-bit, stride 1:  32 channels 0.88, 64 0.72, wider 0.68; INT8 0.85, 0.74, 0.76;
+//   FP32 0.84, 0.65, 0.64; stride 2 past 32 channels 0.50 to 0.71 in every type.
+// 16 channels keep four rows: a 32-channel tile would compute half its products
+// for padding, at the same time or up to 1.38 of it (61 F16 maps 19x88 23.5 us
+// against 15.5).
+//   - A tall tile may pad at most a fifth more rows than the low one: 24 BF16 maps of
+//     10x44, 96 -> 40 channels, in 16-row tiles compute 16 rows for 10.
+//   - INT8 past 32 channels: eight rows only within one full wave (4 maps 28x85, 448 ->
+//     192 channels, 576 workgroups: 80 us, T4_64 52; 12 maps 32x29, 256 -> 96, 288
+//     workgroups: T8_32 31.9, T4_64 32.1, T4_32_K2 40.5).
+//   - FP32 turns to tall tiles last: its matrix steps are longer, so the last wave costs
+//     more (28 maps 82x52 to 32 channels in 16 rows 131 us, in four 100).
+//   - Below the last line the reduction is shared between wavefronts (_K2, _K4): one
+//     workgroup a CU or less, whose own chain is the time.
 static int rule_tile(int dtype, int stride, int cin, int cout, int B, int Ho, int Wo) {
-    constexpr long long kEnough = 400;
     auto wgs = [&](int th, int tn) { return (long long)B * cdiv(Ho, th) * cdiv(Wo, 16) * cdiv(cout, tn); };
+    const int low = stride == 1 ? 4 : 2;
+    auto tall = [&](int th, int tn, int from, int pad = 20) {  // pad: most added rows, in percent
+        return wgs(th, tn) >= from && 100ll * cdiv(Ho, th) * th <= (100ll + pad) * cdiv(Ho, low) * low;
+    };
     const bool f32 = dtype == SV_F32, i8 = dtype == SV_I8;
-    if (stride == 1) {
-        if (cout <= 16) return !f32 && wgs(16, 32) >= kEnough ? T16_32 : T4_16;
-        if (cout <= 32) {
-            if (wgs(16, 32) >= kEnough) return T16_32;
-            if (wgs(8, 32) >= kEnough) return T8_32;
-            if (wgs(4, 32) >= kEnough) return T4_32;
-            return f32 || cin >= 96 ? T4_16_K2 : T4_16;
-        }
-        if (!i8 && wgs(8, 64) >= kEnough) return T8_64;
-        if (wgs(8, 32) >= kEnough) return T8_32;
-        if (wgs(4, 32) >= kEnough) return T4_32_K2;
-        return f32 ? T4_16_K4 : T2_32_K2;
+    if (cout <= 16) return T4_16;
+    if (stride == 2) {
+        if (cout <= 32) return wgs(4, 32) >= 256 ? T4_32 : T4_16;
+        if (i8 && tall(8, 32, 300)) return T8_32;
+        if (f32 && wgs(4, 32) >= 1600) return T4_32;
+        if (wgs(2, 64) >= 256) return T2_64;
+        return f32 || cin >= 64 ? T2_32_K2 : T4_16;
     }
-    if (cout <= 32) return wgs(4, 32) >= kEnough ? T4_32 : T4_16;
-    if (i8 && wgs(8, 32) >= kEnough) return T8_32;
-    if (wgs(2, 64) >= kEnough) return f32 && wgs(4, 32) >= 4 * kEnough ? T4_32 : T2_64;
-    if (cin >= 64 && wgs(2, 64) >= kEnough / 2) return T2_64;
-    return f32 || cin >= 64 ? T2_32_K2 : T4_16;
+    if (f32) {
+        if (cout <= 32) {
+            if (tall(16, 32, 700)) return T16_32;
+            if (tall(8, 32, 700)) return T8_32;
+            if (wgs(4, 32) >= 400) return T4_32;
+            return wgs(4, 16) >= 300 ? T4_16 : T4_16_K2;
+        }
+        if (tall(8, 64, 700)) return T8_64;
+        if (cout > 64 && tall(8, 32, 400)) return T8_32;
+        if (wgs(4, 32) >= (cout <= 64 ? 1024 : 400)) return T4_32;
+        return wgs(4, 16) >= 512 ? T4_16 : T4_16_K4;
+    }
+    if (cout <= 32) {
+        if (tall(16, 32, 400)) return T16_32;
+        if (tall(8, 32, i8 ? 300 : (cin > 32 ? 400 : 700))) return T8_32;
+        return wgs(4, 32) >= 400 ? T4_32 : T4_16;
+    }
+    if (i8) {
+        if (tall(16, 32, 320)) return T16_32;
+        if (tall(8, 32, 256) && wgs(8, 32) <= 512) return T8_32;
+        if (wgs(4, 64) >= 256) return T4_64;
+        return wgs(4, 32) >= 256 ? T4_32_K2 : T2_32_K2;
+    }
+    if (tall(8, 64, 256, cout > 64 ? 34 : 20)) return T8_64;
+    if (tall(8, 32, 300)) return T8_32;
+    if (wgs(4, 32) >= 512) return T4_32;
+    return wgs(4, 32) >= 256 ? T4_32_K2 : T4_16_K2;
 }
 
 // Batches whose images times channel tiles pass a grid's 65535 planes in a narrow

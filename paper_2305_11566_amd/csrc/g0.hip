@@ -608,13 +608,24 @@ sv_status launch_g0_d(int th, const ConvParams &p, int grid, hipStream_t st) {
 // the weights would not fit the registers.
 bool g0_fits(int dtype, int c1) { return dtype != SV_F32 && c1 <= 32 && c1 % 8 == 0; }
 
-// The rows a tile follow the layer's tuned or ruled tile (the cost of a small
-// tile here is the general kernel's: its halo): 64 maps of bf16 take 114 us in
-// 16 rows and in 8, the uneven batch 69 and 77, 8 INT8 maps 25.8 and 28.7.
+// The rows a tile: a tuned layer's follow its tile (the cost of a small tile here is the
+// general kernel's: its halo), any other's the number of workgroups, at least 400 of
+// them (1.5 a CU) as in the tile rule, with at most a fifth more rows than four would
+// compute.  Sixteen rows past 16 channels alone (8 INT8 maps of 94x311, 32 channels:
+// 25.8 us against 28.7 in eight): with fewer a group's sums are too short a part of its
+// time.  Over 451 sizes of 8 to 32 channels 1.02 of the best height on average, four rows
+// throughout 1.08; sixteen rows at 8 and 16 channels 1.04 to 1.07.
 int g0_tile_h(int cfg) {
     int th, tn;
     conv_cfg_tile(cfg, th, tn);
     return th < 8 ? 4 : th < 16 ? 8 : 16;
+}
+
+int g0_default_h(int c1, int B, int Ho, int Wo) {
+    auto fits = [&](int th) {
+        return (long long)B * cdiv(Ho, th) * cdiv(Wo, 16) >= 400 && 5ll * cdiv(Ho, th) * th <= 24ll * cdiv(Ho, 4);
+    };
+    return c1 > 16 && fits(16) ? 16 : fits(8) ? 8 : 4;
 }
 
 sv_status launch_g0(int dtype, int th, const ConvParams &p, int grid, hipStream_t st) {

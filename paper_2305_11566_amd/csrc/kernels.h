@@ -307,10 +307,12 @@ bool conv_cfg_projects(int cfg, int cout);
 // G0 with the projection epilogue as a kernel of its own (g0.hip): p as for
 // launch_conv with proj_out set, src[0] the resized level below (its storage
 // dtype, pitch = C), src[1] x0.  g0_fits: the dtypes and channel counts it
-// takes; g0_tile_h: its rows a tile for configuration cfg; grid > 0: persistent
+// takes; g0_tile_h: its rows a tile for configuration cfg, g0_default_h: where nothing
+// was tuned; grid > 0: persistent
 // over p.tab's tiles of stage p.stage.
 bool g0_fits(int dtype, int c1);
 int g0_tile_h(int cfg);
+int g0_default_h(int c1, int B, int Ho, int Wo);
 sv_status launch_g0(int dtype, int th, const ConvParams &p, int grid, hipStream_t s);
 // A stride-2 transposed convolution of src[0], the map itself (tconv.hip):
 // the ks x ks correlation of its zero-inserted view, Ho x Wo outputs.  Weights,

@@ -66,6 +66,8 @@ int net_default_cfg(const NetShape &ns, int layer, const Levels &lv, int B);
 // th4_tn64; never split.
 bool net_projects(const NetShape &ns, bool train);
 int net_g0_proj_cfg(const NetShape &ns, int cfg);
+// The rows a tile of G0's own kernel (g0_fits) where configuration cfg stands.
+int net_g0_rows(const NetShape &ns, int cfg, const Levels &lv, int B);
 // The built-in choice for a layer, ignoring overrides and the autotune cache.
 int net_heuristic_cfg(const NetShape &ns, int layer, const Levels &lv, int B);
 // Per-layer tile configuration of a forward pass of batch B at H x W: an

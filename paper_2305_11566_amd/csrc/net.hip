@@ -149,6 +149,11 @@ int net_g0_proj_cfg(const NetShape &ns, int cfg) {
     return c;
 }
 
+int net_g0_rows(const NetShape &ns, int cfg, const Levels &lv, int B) {
+    if (cfg == net_heuristic_cfg(ns, L_G0, lv, B)) return g0_default_h(ns.c1, B, lv.h[0], lv.w[0]);
+    return g0_tile_h(cfg % conv_num_tiles());
+}
+
 int net_default_cfg(const NetShape &ns, int layer, const Levels &lv, int B) {
     const int ov = net_get_cfg_override(ns.dtype, layer);
     if (ov >= 0 && ov < conv_num_cfgs()) return ov;
@@ -419,7 +424,7 @@ sv_status net_forward(const NetShape &ns, const void *packed, const uint8_t *dis
             p.proj_disp = disp;
             p.proj_img = img;
             p.proj_scale0 = (float)ns.f / 256.0f;
-            if (g0_fits(ns.dtype, c1)) SV_STAGE(launch_g0(ns.dtype, g0_tile_h(cfg[L_G0] % conv_num_tiles()), p, 0, st));
+            if (g0_fits(ns.dtype, c1)) SV_STAGE(launch_g0(ns.dtype, net_g0_rows(ns, cfg[L_G0], lv, B), p, 0, st));
             else SV_STAGE(launch_conv(ns.dtype, 3, 1, net_g0_proj_cfg(ns, cfg[L_G0]), p, st));
         }
         ev_rec(8, 1, st);

@@ -36,6 +36,25 @@ def test_larger_grids_take_taller_tiles(monkeypatch, tmp_path):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16", "i8"])
+@pytest.mark.parametrize("c,latent", [((16, 32, 64), 64), ((40, 96, 256), 128)])
+def test_tall_tiles_where_few_rows_are_padded(monkeypatch, tmp_path, dtype, c, latent):
+    """A tall tile's rows, whole tiles, are at most a third more than four-row (two-row at
+    stride 2) tiles would compute: many maps of 9 or 10 rows are no reason for 16."""
+    monkeypatch.setenv("SV_AUTOTUNE_CACHE", str(tmp_path / "none.tsv"))
+    levels = (1, 2, 3, 3, 3, 2, 1, 0)  # 0: the network's working size, each next one half
+    for h in (4, 9, 10, 17, 18, 19, 33, 37, 40, 72, 128):
+        ho = [h]
+        for _ in range(3):
+            ho.append(-(-ho[-1] // 2))
+        for B in (1, 8, 64, 300):
+            for i, n in enumerate(_names(c, latent, 1, dtype, B, h, 200)[:8]):
+                th, rows = int(n[2:].split("_")[0]), ho[levels[i]]
+                low = 2 if i in (0, 1, 2) else 4
+                if th > 4:
+                    assert 3 * -(-rows // th) * th <= 4.1 * -(-rows // low) * low, (n, i, B, h)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16", "i8"])
 @pytest.mark.parametrize("c,latent", [((8, 8, 128), 8), ((16, 64, 64), 64), ((40, 96, 256), 128), ((72, 136, 200), 8)])
 def test_large_batches_keep_within_a_grid(monkeypatch, tmp_path, dtype, c, latent):
     """Images times channel tiles of a launch are at most 65535: a batch that 64

@@ -104,14 +104,50 @@ __device__ __forceinline__ void conv_bias4(const ConvParams &p, int nbase, float
     for (int i = 0; i < 4; ++i) b[i] = (p.bias && nbase + i < p.Cout) ? p.bias[nbase + i] : 0.f;
 }
 
+// The backward terms of channels nbase .. nbase + 3, by one load where they lie
+// aligned: what is added, and the map whose sign is the mask (channels past Cout keep v).
+__device__ __forceinline__ void conv_add4(const ConvParams &p, size_t pix, int nbase, float (&v)[4]) {
+    const float *q = p.add + (pix * p.add_pitch + p.add_coff + nbase);
+    if (nbase + 4 <= p.Cout && (uintptr_t)q % 16 == 0) {
+        const f32x4 e = *(const f32x4 *)q;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = e[i];
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (nbase + i < p.Cout) v[i] = q[i];
+    }
+}
+
+template <int DT>
+__device__ __forceinline__ void conv_mask4(const ConvParams &p, size_t pix, int nbase, float (&v)[4]) {
+    using T = typename Elem<DT>::T;
+    typedef T T4 __attribute__((ext_vector_type(4)));
+    const T *q = (const T *)p.mask + (pix * p.mask_pitch + nbase);
+    if (nbase + 4 <= p.Cout && (uintptr_t)q % sizeof(T4) == 0) {
+        const T4 e = *(const T4 *)q;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const T x = e[i];
+            v[i] = Elem<DT>::load(&x);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (nbase + i < p.Cout) v[i] = Elem<DT>::load(q + i);
+    }
+}
+
 // Returns max |stored value| over the channels it wrote (for amax_out).
-// The backward terms of the four channels by one load each where they lie aligned,
-// behind one test that a forward launch skips: with a test a channel a forward pass
-// took 1 to 2 % longer (table network, 1242x375 FP32: 135.6 us against 131.7); loaded
-// ahead of the sums, or with a test of the mask's window for each channel, they cost
-// every general kernel three to four registers and some a wave a SIMD (FP32 G0 of the
-// 256x128 network, 28 maps 206x328: 264 us against 228).
-template <int DT0>
+// EARLY: the backward terms are loaded ahead of the sums, for the transposed and the
+// general 5x5 convolutions (k_tconv of a BF16 table network's training step 20.2 us
+// against 23.3 after them, 5x5 k_conv 8.0 against 8.2).  Elsewhere after them: ahead
+// they take every 3x3 general kernel three to four registers and some a wave a SIMD
+// (FP32 G0 of the 256x128 network, 28 maps 206x328: 264 us against 228), and the row
+// kernel's forward layers 1 % (16 pairs of the BF16 table network 211 us a call, 208).
+// One test of the map and one of the window for four channels: a test a channel cost
+// forward launches 1 to 2 % (FP32 table network, 1242x375: 135.6 us against 132.9).
+template <int DT0, bool EARLY = false>
 __device__ __forceinline__ float conv_epilogue(const ConvParams &p, size_t pix, int nbase,
                                                const float (&acc)[4], const float (&bias)[4]) {
     constexpr int DT = Store<DT0>::v;
@@ -119,39 +155,27 @@ __device__ __forceinline__ float conv_epilogue(const ConvParams &p, size_t pix, 
     float r[4];
     const bool full = nbase + 4 <= p.Cout;
     constexpr bool BWD = DT0 != SV_I8;  // (INT8 has no backward terms)
+    const bool adds = BWD && p.add, masks = BWD && p.mask && nbase >= p.mask_lo && nbase < p.mask_hi;
+    float add[4] = {0.f, 0.f, 0.f, 0.f}, mv[4] = {1.f, 1.f, 1.f, 1.f};
+    if (EARLY && adds) conv_add4(p, pix, nbase, add);
+    if (EARLY && masks) conv_mask4<DT>(p, pix, nbase, mv);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         float val = acc[i] + bias[i];
         if (p.act) val = val > 0.f ? val : 0.1f * val;
+        if (EARLY && BWD && p.add) val += add[i];
+        if (EARLY && BWD && p.mask) val *= mv[i] > 0.f ? 1.0f : 0.1f;
         r[i] = val;
     }
-    if (BWD && p.add) {
-        const float *q = p.add + (pix * p.add_pitch + p.add_coff + nbase);
-        if (full && (uintptr_t)q % 16 == 0) {
-            const f32x4 v = *(const f32x4 *)q;
+    if (!EARLY && adds) {
+        conv_add4(p, pix, nbase, add);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) r[i] += v[i];
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (nbase + i < p.Cout) r[i] += q[i];
-        }
+        for (int i = 0; i < 4; ++i) r[i] += add[i];
     }
-    if (BWD && p.mask && nbase >= p.mask_lo && nbase < p.mask_hi) {
-        typedef T T4 __attribute__((ext_vector_type(4)));
-        const T *q = (const T *)p.mask + (pix * p.mask_pitch + nbase);
-        if (full && (uintptr_t)q % sizeof(T4) == 0) {
-            const T4 v = *(const T4 *)q;
+    if (!EARLY && masks) {
+        conv_mask4<DT>(p, pix, nbase, mv);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const T e = v[i];
-                r[i] *= Elem<DT>::load(&e) > 0.f ? 1.0f : 0.1f;
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (nbase + i < p.Cout) r[i] *= Elem<DT>::load(q + i) > 0.f ? 1.0f : 0.1f;
-        }
+        for (int i = 0; i < 4; ++i) r[i] *= mv[i] > 0.f ? 1.0f : 0.1f;
     }
     const size_t o = pix * p.out_pitch + p.out_coff + nbase;
     float amax = 0.f;
@@ -919,7 +943,7 @@ struct ConvTile {
                         *(f32x4 *)&p.part[((size_t)kz * p.B * G.Ho * G.Wo + pix) * p.n_pad + nbase] = av;
                 } else {
                     const float r[4] = {av[0], av[1], av[2], av[3]};
-                    lmax = fmaxf(lmax, conv_epilogue<DT>(p, pix, nbase, r, bpre[nb]));
+                    lmax = fmaxf(lmax, conv_epilogue<DT, KS == 5>(p, pix, nbase, r, bpre[nb]));
                 }
             }
         }

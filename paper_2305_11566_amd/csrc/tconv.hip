@@ -171,7 +171,7 @@ __global__ void __launch_bounds__(256) k_tconv(const ConvParams p, int tiles_x, 
 #pragma unroll
         for (int n = 0; n < NB; ++n) {
             const float v[4] = {acc[m][n][0], acc[m][n][1], acc[m][n][2], acc[m][n][3]};
-            conv_epilogue<DT>(p, pix, n0 + 16 * n + 4 * g, v, bias[n]);
+            conv_epilogue<DT, true>(p, pix, n0 + 16 * n + 4 * g, v, bias[n]);
         }
     }
 }
